@@ -1,6 +1,6 @@
 // Row-wise kernels (gfx950): embedding gather, RMSNorm, row gathers, weight
 // repacking and the output-head finalisation (log-sum-exp, greedy argmax,
-// in-place log-softmax).
+// in-place log-softmax, top-8 labels).
 #pragma once
 
 #include "device_common.hpp"
@@ -259,15 +259,10 @@ __global__ __launch_bounds__(256) void scatter_rows_kernel(char* __restrict__ ds
 //   written by the output-head GEMM.  Outputs go to index o = perm[r] * block + s
 //   (the caller's anchor order).  The row's max and sum(exp(z - max)) come from
 //   the GEMM epilogue's per-group partials (part[r * part_ld + g], g < part_ld =
-//   V / 64) when part is set, and the argmax (ties -> lowest id) is then the
-//   first column equal to the max, found in the pass below; without partials a
-//   first pass over the logits gives all three.  Then one pass rewrites the row
-//   as z - LSE (write_lp) and, with TOPK, keeps each thread's 8 best (value, id)
-//   pairs, ranked by decreasing value and then increasing id, while summing
-//   exp(z - max) over every entry the thread drops from (or never admits to)
-//   that list; eight block-wide argmax rounds merge the lists into the row's
-//   top 8, and the entries left in the lists join the sum, which is then the
-//   mass of exactly the tokens ranked after the 8th (the tail bucket).
+//   V / 64).  With TOPK the 8 best tokens and the tail come from the partials and
+//   eight 64-column groups of logits (row_top8), and the greedy token is the first
+//   of them; without, it is the first column equal to the max, found in the pass
+//   that rewrites the row as z - LSE (write_lp).
 //   next_tok[r] = forced[o] if that is >= 0, else the argmax.  target_logp[o]
 //   = log p(target[r]) (nan when target[r] < 0).  A row with valid[r] == 0 gets
 //   token -1, top ids -1, top log-probs -inf, tail 0, target log-prob nan and,
@@ -290,21 +285,21 @@ struct LmFinalize {
   const int* target;   // [r] or null
   float* target_logp;  // [o] (with target)
   const unsigned char* valid;  // [r] or null
-  const LogitPart* part;       // [r * part_ld + g] or null
+  const LogitPart* part;       // [r * part_ld + g]
   int part_ld;
 };
 
-struct MaxArg {
+// Running max and sum of exponentials relative to it.
+struct MaxSum {
   float m, s;
-  int i;
 };
-__device__ __forceinline__ MaxArg merge_maxarg(MaxArg a, MaxArg b) {
-  if (b.m > a.m || (b.m == a.m && b.i < a.i)) {
+__device__ __forceinline__ MaxSum merge_maxsum(MaxSum a, MaxSum b) {
+  if (b.m > a.m) {
     const float sa = (a.m == -INFINITY) ? 0.f : a.s * expf(a.m - b.m);
-    return {b.m, sa + b.s, b.i};
+    return {b.m, sa + b.s};
   }
   const float sb = (b.m == -INFINITY) ? 0.f : b.s * expf(b.m - a.m);
-  return {a.m, a.s + sb, a.i};
+  return {a.m, a.s + sb};
 }
 
 // (v, i) ranks before (w, j): larger value, then lower id
@@ -312,13 +307,183 @@ __device__ __forceinline__ bool ranks_before(float v, int i, float w, int j) {
   return v > w || (v == w && i < j);
 }
 
+// Max and sum of exponentials over a row's n partials, in every thread of a
+// 256-thread workgroup (the loads go out four at a time before their uses).
+__device__ __forceinline__ MaxSum row_maxsum(const LogitPart* pr, int n, MaxSum* red) {
+  constexpr int U = 4;
+  MaxSum acc = {-INFINITY, 0.f};
+  for (int g0 = threadIdx.x; g0 < n; g0 += 256 * U) {
+    LogitPart q[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (g0 + u * 256 < n) q[u] = pr[g0 + u * 256];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (g0 + u * 256 < n) acc = merge_maxsum(acc, MaxSum{q[u].m, q[u].s});
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    MaxSum b;
+    b.m = __shfl_xor(acc.m, off);
+    b.s = __shfl_xor(acc.s, off);
+    acc = merge_maxsum(acc, b);
+  }
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  MaxSum t = red[0];
+#pragma unroll
+  for (int w = 1; w < 4; ++w) t = merge_maxsum(t, red[w]);
+  return t;
+}
+
+struct Top8 {
+  float v[ALR_K_TOP];
+  int i[ALR_K_TOP];
+};
+struct Top8Scratch {
+  Top8 groups, top;  // the eight best groups, the eight best entries
+  float win_v[4], rest[4];
+  int win_i[4];
+};
+
+// The 8 best (value, id) pairs of the workgroup's threads' lists, ranked, into
+// out; each list (L entries) is ranked itself, and is popped as its entries win.
+// Lists end with id 0x7FFFFFFF, value -inf.
+template <int L>
+__device__ __forceinline__ void block_pop8(float (&tv)[L], int (&ti)[L], Top8& out, float* win_v,
+                                           int* win_i) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int k = 0; k < ALR_K_TOP; ++k) {
+    float bv = tv[0];
+    int bi = ti[0];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      const float ov = __shfl_xor(bv, off);
+      const int oi = __shfl_xor(bi, off);
+      if (ranks_before(ov, oi, bv, bi)) {
+        bv = ov;
+        bi = oi;
+      }
+    }
+    if (lane == 0) {
+      win_v[wave] = bv;
+      win_i[wave] = bi;
+    }
+    __syncthreads();
+    float wv = win_v[0];
+    int wi = win_i[0];
+#pragma unroll
+    for (int w = 1; w < 4; ++w)
+      if (ranks_before(win_v[w], win_i[w], wv, wi)) {
+        wv = win_v[w];
+        wi = win_i[w];
+      }
+    if (threadIdx.x == 0) {
+      out.v[k] = wv;
+      out.i[k] = wi;
+    }
+    if (ti[0] == wi && wi != 0x7FFFFFFF) {  // ids are unique: the owner pops its head
+#pragma unroll
+      for (int j = 0; j < L - 1; ++j) {
+        tv[j] = tv[j + 1];
+        ti[j] = ti[j + 1];
+      }
+      tv[L - 1] = -INFINITY;
+      ti[L - 1] = 0x7FFFFFFF;
+    }
+    __syncthreads();  // win_v / win_i are rewritten in the next round
+  }
+}
+
+// The row's 8 best tokens (decreasing logit, then increasing id) in sc.top, and
+// the sum of exp(z - m) over every other token as the return value (the same in
+// all 256 threads), from the row's n partials pr and its logits z; m >= every
+// logit.  Any token outside the 8 groups with the largest maxima (ties to the
+// lower group) has 8 tokens ranked before it, those groups' maxima, so the
+// logits of just those groups are read, 2 KB instead of the whole row.  A pass over
+// the rows with an insertion list per thread took 248 us at 192 rows of 152064 (29 M
+// logits); a panel of 1206 rows x 24064 columns, as many logits, takes 33 us.  What
+// bounds it is the chain of 16 block-wide picks.  The sum adds the other groups' partial sums and the unselected
+// entries of these, so nothing cancels.  Ids and column 0 are relative to z.
+__device__ __forceinline__ float row_top8(const LogitPart* pr, int n, const float* z, float m,
+                                          Top8Scratch& sc) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  {
+    float tv[ALR_K_TOP];
+    int ti[ALR_K_TOP];
+#pragma unroll
+    for (int j = 0; j < ALR_K_TOP; ++j) {
+      tv[j] = -INFINITY;
+      ti[j] = 0x7FFFFFFF;
+    }
+    for (int g = threadIdx.x; g < n; g += 256) {
+      const float gm = pr[g].m;
+      // groups rise within a thread: an equal max ranks after the ones held
+      if (gm > tv[ALR_K_TOP - 1] || ti[ALR_K_TOP - 1] == 0x7FFFFFFF) {
+        float pv = gm;
+        int pi = g;
+        bool sh = false;
+#pragma unroll
+        for (int j = 0; j < ALR_K_TOP; ++j) {
+          const bool take = sh || gm > tv[j] || ti[j] == 0x7FFFFFFF;
+          if (take) {
+            const float ov = tv[j];
+            const int oi = ti[j];
+            tv[j] = pv;
+            ti[j] = pi;
+            pv = ov;
+            pi = oi;
+          }
+          sh = take;
+        }
+      }
+    }
+    block_pop8<ALR_K_TOP>(tv, ti, sc.groups, sc.win_v, sc.win_i);
+  }
+  int sel[ALR_K_TOP];
+#pragma unroll
+  for (int j = 0; j < ALR_K_TOP; ++j) sel[j] = sc.groups.i[j];  // 0x7FFFFFFF past the last group
+  float rest = 0.f;
+  for (int g = threadIdx.x; g < n; g += 256) {
+    bool in = false;
+#pragma unroll
+    for (int j = 0; j < ALR_K_TOP; ++j) in |= g == sel[j];
+    const LogitPart q = pr[g];
+    if (!in && q.m != -INFINITY) rest = fmaf(q.s, expf(q.m - m), rest);
+  }
+  // thread t holds column t % 64 of the groups t / 64 and t / 64 + 4
+  float ev[2];
+  int ei[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int g = sc.groups.i[wave + 4 * h];
+    const bool have = g < n;
+    ei[h] = have ? g * 64 + lane : 0x7FFFFFFF;
+    ev[h] = have ? z[ei[h]] : -INFINITY;
+  }
+  if (ranks_before(ev[1], ei[1], ev[0], ei[0])) {
+    const float v = ev[0];
+    const int i = ei[0];
+    ev[0] = ev[1];
+    ei[0] = ei[1];
+    ev[1] = v;
+    ei[1] = i;
+  }
+  block_pop8<2>(ev, ei, sc.top, sc.win_v, sc.win_i);
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    if (ei[h] != 0x7FFFFFFF) rest += expf(ev[h] - m);
+  rest = wave_sum(rest);
+  if (lane == 0) sc.rest[wave] = rest;
+  __syncthreads();
+  return ((sc.rest[0] + sc.rest[1]) + sc.rest[2]) + sc.rest[3];
+}
+
 template <bool TOPK>
 __global__ __launch_bounds__(256) void lm_finalize_kernel(LmFinalize a) {
-  __shared__ MaxArg red[4];
-  __shared__ float lse_sh, m_sh, s_sh, tgt_sh;
-  __shared__ float win_v[4], top_v[ALR_K_TOP];
-  __shared__ int win_i[4], top_i[ALR_K_TOP];
-  __shared__ float tail_red[4];
+  __shared__ MaxSum red[4];
+  __shared__ Top8Scratch sc;
+  __shared__ int arg_red[4];
   const int r = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const long orow = a.perm[r];
@@ -340,49 +505,9 @@ __global__ __launch_bounds__(256) void lm_finalize_kernel(LmFinalize a) {
       for (int c = threadIdx.x; c < V; c += blockDim.x) z[c] = -INFINITY;
     return;
   }
-  MaxArg acc = {-INFINITY, 0.f, 0x7FFFFFFF};
-  const bool from_part = a.part != nullptr;
-  // Loads go out four at a time before their uses (one memory round trip per
-  // four, where a load used in the same iteration costs one each); every
-  // thread still visits its groups and columns in increasing order.
-  constexpr int U = 4;
-  if (from_part) {
-    const LogitPart* pr = a.part + (long)r * a.part_ld;
-    for (int g0 = threadIdx.x; g0 < a.part_ld; g0 += blockDim.x * U) {
-      LogitPart q[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (g0 + u * (int)blockDim.x < a.part_ld) q[u] = pr[g0 + u * blockDim.x];
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (g0 + u * (int)blockDim.x < a.part_ld)
-          acc = merge_maxarg(acc, MaxArg{q[u].m, q[u].s, 0x7FFFFFFF});
-    }
-  } else {
-    for (int c = threadIdx.x * 4; c < V; c += blockDim.x * 4) {
-      const f32x4 v = *(const f32x4*)(z + c);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (v[e] > acc.m) {
-          acc.s = (acc.m == -INFINITY) ? 1.f : acc.s * expf(acc.m - v[e]) + 1.f;
-          acc.m = v[e];
-          acc.i = c + e;
-        } else {
-          acc.s += expf(v[e] - acc.m);
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    MaxArg b;
-    b.m = __shfl_xor(acc.m, off);
-    b.s = __shfl_xor(acc.s, off);
-    b.i = __shfl_xor(acc.i, off);
-    acc = merge_maxarg(acc, b);
-  }
-  if (lane == 0) red[wave] = acc;
-  __syncthreads();
+  const LogitPart* pr = a.part + (long)r * a.part_ld;
+  const MaxSum ms = row_maxsum(pr, a.part_ld, red);
+  const float m = ms.m, lse = ms.m + logf(ms.s);
   // the greedy token (or the forced one) goes out once the argmax is known
   auto emit_token = [&](int arg) {
     if (a.tokens) a.tokens[o] = arg;
@@ -395,35 +520,30 @@ __global__ __launch_bounds__(256) void lm_finalize_kernel(LmFinalize a) {
       a.next_tok[r] = nxt;
     }
   };
-  if (threadIdx.x == 0) {
-    MaxArg t = red[0];
-    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) t = merge_maxarg(t, red[w]);
-    lse_sh = t.m + logf(t.s);
-    m_sh = t.m;
-    s_sh = t.s;
-    if (!from_part) emit_token(t.i);
-    if (a.target) {
-      const int x = a.target[r];
-      tgt_sh = (x >= 0) ? z[x] : __builtin_nanf("");
+  float tgt = 0.f;
+  if (a.target && threadIdx.x == 0) {
+    const int x = a.target[r];
+    tgt = (x >= 0) ? z[x] : __builtin_nanf("");
+  }
+  if constexpr (TOPK) {
+    const float rest = row_top8(pr, a.part_ld, z, m, sc);
+    if (threadIdx.x == 0) {
+      a.tail[o] = rest / ms.s;
+      emit_token(min(sc.top.i[0], V - 1));
+    }
+    if (threadIdx.x < ALR_K_TOP) {
+      const float v = sc.top.v[threadIdx.x];
+      const bool have = v != -INFINITY;
+      a.top_ids[o * ALR_K_TOP + threadIdx.x] = have ? sc.top.i[threadIdx.x] : -1;
+      a.top_logp[o * ALR_K_TOP + threadIdx.x] = have ? v - lse : -INFINITY;
     }
   }
-  __syncthreads();
-  const float lse = lse_sh, m = m_sh;
-  if (!a.write_lp && !TOPK && !from_part) {
-    if (a.target && threadIdx.x == 0) a.target_logp[o] = tgt_sh - lse;
-    return;
-  }
-  float tv[ALR_K_TOP];
-  int ti[ALR_K_TOP];
-#pragma unroll
-  for (int j = 0; j < ALR_K_TOP; ++j) {
-    tv[j] = -INFINITY;
-    ti[j] = 0x7FFFFFFF;
-  }
-  float tsum = 0.f;  // exp(z - m) of the entries this thread dropped or never admitted
   int arg = 0x7FFFFFFF;  // this thread's first column equal to the row max
   const int cstep = blockDim.x * 4;
-  if constexpr (!TOPK) {
+  constexpr int U = 4;
+  if (!TOPK || a.write_lp) {
+    // thread 0's target logit is read before any thread rewrites the row
+    __syncthreads();
     // no data-dependent branch in the source: the loads of a round are
     // unconditional (a column past V re-reads the row's last chunk, unused)
     // and the argmax update is a select
@@ -437,129 +557,150 @@ __global__ __launch_bounds__(256) void lm_finalize_kernel(LmFinalize a) {
         const bool in = c < V;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          arg = (in && arg == 0x7FFFFFFF && vv[u][e] == m) ? c + e : arg;  // columns rise
+          if constexpr (!TOPK)
+            arg = (in && arg == 0x7FFFFFFF && vv[u][e] == m) ? c + e : arg;  // columns rise
           vv[u][e] -= lse;
         }
         if (in && a.write_lp) *(f32x4*)(z + c) = vv[u];
       }
     }
-  } else {
-    for (int c0 = threadIdx.x * 4; c0 < V; c0 += cstep * U) {
-      f32x4 vv[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (c0 + u * cstep < V) vv[u] = *(const f32x4*)(z + c0 + u * cstep);
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int c = c0 + u * cstep;
-        if (c >= V) break;
-        f32x4 v = vv[u];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          if (arg == 0x7FFFFFFF && v[e] == m) arg = c + e;  // columns rise within a thread
-          // this thread meets ids in increasing order, so an equal value ranks
-          // after the entries already held: admit only strictly larger values
-          if (v[e] > tv[ALR_K_TOP - 1]) {
-            const float out_v = tv[ALR_K_TOP - 1];
-            if (out_v != -INFINITY) tsum += expf(out_v - m);
-            float pv = v[e];
-            int pi = c + e;
-            bool sh = false;
-#pragma unroll
-            for (int j = 0; j < ALR_K_TOP; ++j) {
-              const bool take = sh || (v[e] > tv[j]);
-              if (take) {
-                const float ov = tv[j];
-                const int oi = ti[j];
-                tv[j] = pv;
-                ti[j] = pi;
-                pv = ov;
-                pi = oi;
-              }
-              sh = take;
-            }
-          } else {
-            tsum += expf(v[e] - m);
-          }
-          v[e] -= lse;
-        }
-        if (a.write_lp) *(f32x4*)(z + c) = v;
-      }
-    }
   }
-  if (from_part) {  // lowest column holding the max over the block
+  if constexpr (!TOPK) {  // lowest column holding the max over the block
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) arg = min(arg, __shfl_xor(arg, off));
-    if (lane == 0) win_i[wave] = arg;
+    if (lane == 0) arg_red[wave] = arg;
     __syncthreads();
     if (threadIdx.x == 0) {
-      int t = win_i[0];
-      for (int w = 1; w < (int)(blockDim.x >> 6); ++w) t = min(t, win_i[w]);
-      emit_token(t);
-    }
-    __syncthreads();  // win_i is reused by the top-8 rounds
-  }
-  if constexpr (TOPK) {
-    // eight rounds: the best head of all threads' lists is the next entry
-    for (int k = 0; k < ALR_K_TOP; ++k) {
-      float bv = tv[0];
-      int bi = ti[0];
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        const float ov = __shfl_xor(bv, off);
-        const int oi = __shfl_xor(bi, off);
-        if (ranks_before(ov, oi, bv, bi)) {
-          bv = ov;
-          bi = oi;
-        }
-      }
-      if (lane == 0) {
-        win_v[wave] = bv;
-        win_i[wave] = bi;
-      }
-      __syncthreads();
-      if (threadIdx.x == 0) {
-        float wv = win_v[0];
-        int wi = win_i[0];
-        for (int w = 1; w < (int)(blockDim.x >> 6); ++w)
-          if (ranks_before(win_v[w], win_i[w], wv, wi)) {
-            wv = win_v[w];
-            wi = win_i[w];
-          }
-        top_v[k] = wv;
-        top_i[k] = wi;
-      }
-      __syncthreads();
-      if (ti[0] == top_i[k] && tv[0] != -INFINITY) {  // ids are unique: the owner pops its head
-#pragma unroll
-        for (int j = 0; j < ALR_K_TOP - 1; ++j) {
-          tv[j] = tv[j + 1];
-          ti[j] = ti[j + 1];
-        }
-        tv[ALR_K_TOP - 1] = -INFINITY;
-        ti[ALR_K_TOP - 1] = 0x7FFFFFFF;
-      }
-    }
-    // what is left in the lists ranks after the 8th entry
-#pragma unroll
-    for (int j = 0; j < ALR_K_TOP; ++j)
-      if (tv[j] != -INFINITY) tsum += expf(tv[j] - m);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) tsum += __shfl_xor(tsum, off);
-    if (lane == 0) tail_red[wave] = tsum;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      float t = 0.f;
-      for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += tail_red[w];
-      a.tail[o] = t / s_sh;
-    }
-    if (threadIdx.x < ALR_K_TOP) {
-      const bool have = top_v[threadIdx.x] != -INFINITY;
-      a.top_ids[o * ALR_K_TOP + threadIdx.x] = have ? top_i[threadIdx.x] : -1;
-      a.top_logp[o * ALR_K_TOP + threadIdx.x] = have ? top_v[threadIdx.x] - lse : -INFINITY;
+      int t = arg_red[0];
+      for (int w = 1; w < (int)(blockDim.x >> 6); ++w) t = min(t, arg_red[w]);
+      emit_token(min(t, V - 1));
     }
   }
-  if (a.target && threadIdx.x == 0) a.target_logp[o] = tgt_sh - lse;
+  if (a.target && threadIdx.x == 0) a.target_logp[o] = tgt - lse;
+}
+
+// Corpus labels without full log-probs.  A label depends on its position alone,
+// so each distinct token row is labelled once (row u; its token row and whether
+// the sequence ends there are in urow: t, or -1 - t at a sequence's last token)
+// and expanded to the (anchor, slot) pairs at that position afterwards.  The
+// logits of all rows come panel by panel of columns, so that they fit the
+// workspace's logit rows; LabelState carries a row's labels across the panels.
+struct LabelState {
+  Top8 top;
+  float m, s;    // max and sum of exp(z - m) over the columns seen
+  float rest;    // the part of s outside top
+  float target;  // logit of the corpus token that follows (nan until seen)
+};
+
+__global__ __launch_bounds__(256) void label_panel_kernel(const float* __restrict__ z, long z_rs,
+                                                          int col0, const LogitPart* __restrict__ part,
+                                                          int n_groups,
+                                                          const int* __restrict__ urow,
+                                                          const int* __restrict__ ctok,
+                                                          LabelState* __restrict__ state) {
+  __shared__ MaxSum red[4];
+  __shared__ Top8Scratch sc;
+  const int u = blockIdx.x;
+  const LogitPart* pr = part + (long)u * n_groups;
+  const float* zr = z + (long)u * z_rs;
+  const MaxSum ms = row_maxsum(pr, n_groups, red);
+  const float rest = row_top8(pr, n_groups, zr, ms.m, sc);
+  if (threadIdx.x >= 64) return;
+  // the first wave merges: lanes 0-7 hold the panels' so far, lanes 8-15 this one's
+  LabelState& st = state[u];
+  const int lane = threadIdx.x;
+  const bool first = col0 == 0;
+  float v = -INFINITY;
+  int id = 0x7FFFFFFF;
+  if (lane < 8) {
+    if (!first) {
+      v = st.top.v[lane];
+      id = st.top.i[lane];
+    }
+  } else if (lane < 16) {
+    v = sc.top.v[lane - 8];
+    id = sc.top.i[lane - 8];
+    if (id != 0x7FFFFFFF) id += col0;
+  }
+  const MaxSum old = first ? MaxSum{-INFINITY, 0.f} : MaxSum{st.m, st.s};
+  const float old_rest = first ? 0.f : st.rest;
+  float target = first ? __builtin_nanf("") : st.target;
+  const MaxSum tot = merge_maxsum(old, ms);
+  int rank = 0;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const float w = __shfl(v, j);
+    const int k = __shfl(id, j);
+    // entries that pad a list (id 0x7FFFFFFF) rank by lane, after all others
+    rank += (ranks_before(w, k, v, id) || (w == v && k == id && j < lane)) ? 1 : 0;
+  }
+  float drop = (lane < 16 && rank >= 8 && id != 0x7FFFFFFF) ? expf(v - tot.m) : 0.f;
+  drop = wave_sum(drop);
+  if (lane < 16 && rank < 8) {
+    st.top.v[rank] = v;
+    st.top.i[rank] = id;
+  }
+  if (lane == 0) {
+    const float eo = old.m == -INFINITY ? 0.f : expf(old.m - tot.m);
+    const float en = ms.m == -INFINITY ? 0.f : expf(ms.m - tot.m);
+    st.m = tot.m;
+    st.s = tot.s;
+    st.rest = (old_rest * eo + rest * en) + drop;
+    const int t = urow[u];
+    const int x = t >= 0 ? ctok[t + 1] : -1;
+    if (x >= col0 && x < col0 + n_groups * 64) target = zr[x - col0];
+    st.target = target;
+  }
+}
+
+// dst[u, :] = src[token row of u, :] (row_elems elements, whole 16-byte chunks)
+// and uidx[token row] = u.
+template <typename T>
+__global__ __launch_bounds__(256) void label_rows_kernel(T* __restrict__ dst,
+                                                         const T* __restrict__ src,
+                                                         const int* __restrict__ urow,
+                                                         int* __restrict__ uidx, long row_elems) {
+  const int u = blockIdx.x, w = urow[u], t = w >= 0 ? w : -1 - w;
+  const u32x4* sp = (const u32x4*)(src + (long)t * row_elems);
+  u32x4* op = (u32x4*)(dst + (long)u * row_elems);
+  const int nch = (int)(row_elems * sizeof(T) / 16);
+  for (int c = threadIdx.x; c < nch; c += blockDim.x) op[c] = sp[c];
+  if (threadIdx.x == 0) uidx[t] = u;
+}
+
+// Labels of (sorted anchor r, slot s), eight threads each, from the row at its
+// position; past the sequence's end: ids -1, log-probs -inf, tail 0, corpus
+// log-prob nan, as in lm_finalize_kernel.
+__global__ __launch_bounds__(256) void label_expand_kernel(
+    const LabelState* __restrict__ state, const int* __restrict__ uidx,
+    const int* __restrict__ perm, const int* __restrict__ atok, const int* __restrict__ apos,
+    const int* __restrict__ alen, int n, int block, int* __restrict__ tokens,
+    int* __restrict__ top_ids, float* __restrict__ top_logp, float* __restrict__ tail,
+    float* __restrict__ target_logp) {
+  const long q = ((long)blockIdx.x * 256 + threadIdx.x) >> 3;
+  const int e = threadIdx.x & 7;
+  if (q >= (long)n * block) return;
+  const int r = (int)(q / block), s = (int)(q % block);
+  const long o = (long)perm[r] * block + s;
+  int id = -1;
+  float lp = -INFINITY, tl = 0.f, tgt = __builtin_nanf("");
+  if (apos[r] + s <= alen[r] - 1) {
+    const LabelState& st = state[uidx[atok[r] + s]];
+    const float lse = st.m + logf(st.s), v = st.top.v[e];
+    if (v != -INFINITY) {
+      id = st.top.i[e];
+      lp = v - lse;
+    }
+    tl = st.rest / st.s;
+    tgt = st.target - lse;
+  }
+  top_ids[o * ALR_K_TOP + e] = id;
+  top_logp[o * ALR_K_TOP + e] = lp;
+  if (e == 0) {
+    tokens[o] = id;
+    tail[o] = tl;
+    target_logp[o] = tgt;
+  }
 }
 
 // Zero the entries of the transposed V cache that pad each sequence to a

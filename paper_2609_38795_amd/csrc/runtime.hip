@@ -55,7 +55,7 @@ struct Layout {
   size_t feat_store, hf_store;
   size_t resid, xnorm, qbuf, attn, act;
   size_t i_tokpos, i_rowstart, i_perm, i_apos, i_rpos, i_atok, i_aseq, i_alen, i_cur;
-  size_t i_valid, i_target, i_ira, i_ctok, logits, lm_part;
+  size_t i_valid, i_target, i_ira, i_ctok, i_urow, i_uidx, label_state, logits, lm_part;
   size_t i_pwork, i_dwork, i_maps, i_vtcol, i_vtpad, i_rowinfo, i_rowptr;
   size_t part_o, part_ml;
   size_t splitk, splitk_bytes;
@@ -227,9 +227,17 @@ size_t compute_layout(const alr_config& c, const alr_limits& lim, Layout& L) {
   L.i_target = take(NA * 4);
   L.i_ira = take(NA * 2 * 4);
   L.i_ctok = take(T * 4);
-  L.logits = take(NA * V * 4);
-  // output-head partials: one LogitPart per (anchor row, 64-column group)
-  L.lm_part = take(NA * (V / 64) * sizeof(LogitPart));
+  // corpus labels: distinct token rows, their inverse, their labels
+  L.i_urow = take(T * 4);
+  L.i_uidx = take(T * 4);
+  L.label_state = take(T * sizeof(LabelState));
+  // logit rows: one per anchor, and never less than 64 columns of every row the
+  // corpus labels can name (vocabularies below 64 x block); output-head partials:
+  // one LogitPart per 64 of them
+  const size_t label_rows = std::min(T, NA * (size_t)lim.max_block);
+  const size_t logit_vals = std::max(NA * V, label_rows * 64);
+  L.logits = take(logit_vals * 4);
+  L.lm_part = take(logit_vals / 64 * sizeof(LogitPart));
   L.max_pwork = ((T + 31) / 32 + lim.max_seqs) * H + (size_t)lim.max_seqs * G;
   const size_t ag = (size_t)anchor_group(c);
   L.max_groups = (NA + ag - 1) / ag + std::min<size_t>(lim.max_seqs, NA);
@@ -320,6 +328,7 @@ struct alr_ctx {
   std::vector<PrefillItem> h_pwork;
   std::vector<int> h_anch;  // perm | apos | atok | aseq | alen (n each) | rope positions (3n)
   std::vector<int> h_ira;   // secondary primaries | offsets
+  std::vector<int> h_urow;  // corpus labels: distinct token rows (-1 - t at a sequence's end)
   std::vector<DecodeItem> h_dwork;
   std::vector<DecodeGroup> h_groups;
   std::vector<int> h_grprow, h_rowinfo;
@@ -1015,15 +1024,63 @@ alr_status run_rollout(alr_ctx* ctx, int n, int block, const int32_t* forced, co
   return ALR_OK;
 }
 
-// Corpus labels: for every slot s, the prefill's final-norm rows at a + s
-// through the output head, the corpus token's log-prob, then the gates.
+alr_status upload(alr_ctx* ctx, void* dst, const void* src, size_t bytes, hipStream_t st) {
+  if (bytes == 0) return ALR_OK;
+  ALR_HIP(ctx, hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st));
+  return ALR_OK;
+}
+
+// Corpus labels: the prefill's final-norm rows at a + s through the output head,
+// the corpus token's log-prob, then the gates.  Without full log-prob rows every
+// distinct position is labelled once, all of them in one product per panel of
+// columns (LabelState); a panel is as wide as the workspace's logit rows
+// (max_anchors x vocab values) allow, so there are never more products than
+// slots.  At 2 x 96 anchors x 16 slots of 2 x 1024 tokens (d 3584, vocab 152064)
+// that is 1,206 rows in 7 products instead of 16 products of 192 rows that each
+// read the whole 1.09 GB head (9.5 -> 1.7 ms per call).  Full log-prob rows go slot by slot, where the
+// product writes the caller's rows itself.
 template <typename T>
 alr_status corpus_impl(alr_ctx* ctx, int n, int block, const LabelDst& out, float* corpus_logp,
                        float* gate_soft, float* gate_hard, hipStream_t st) {
   const alr_config& c = ctx->cfg;
   const Layout& L = ctx->L;
-  const int d = c.d_model;
-  for (int s = 0; s < block; ++s) {
+  const int d = c.d_model, V = c.vocab;
+  if (!out.logprobs) {
+    const int D = (int)ctx->h_urow.size();
+    const int* urow = ctx->at<int>(L.i_urow);
+    LabelState* state = ctx->at<LabelState>(L.label_state);
+    const alr_status stt = upload(ctx, ctx->at<int>(L.i_urow), ctx->h_urow.data(), (size_t)D * 4, st);
+    if (stt != ALR_OK) return stt;
+    label_rows_kernel<T><<<D, 256, 0, st>>>(ctx->at<T>(L.xnorm), ctx->at<T>(L.hf_store), urow,
+                                            ctx->at<int>(L.i_uidx), d);
+    ALR_LAUNCHED(ctx, "corpus rows");
+    // whole 256-column tiles where they fit, and at least one 64-column group
+    const long fit = (long)ctx->lim.max_anchors * V / D;
+    const long unit = fit >= 256 ? 256 : 64;
+    const int wide = (int)std::min<long>(V, std::max<long>(unit, fit / unit * unit));
+    for (int c0 = 0; c0 < V; c0 += wide) {
+      const int w = std::min(wide, V - c0);
+      EpiLogits el;
+      el.out = ctx->at<float>(L.logits);
+      el.rs = w;
+      el.perm = nullptr;
+      el.part = ctx->at<LogitPart>(L.lm_part);
+      el.part_ld = w / 64;
+      launch_gemm<ALR_PROF_LM_GEMM, T>(ctx, ctx->at<T>(L.xnorm), d,
+                                       ctx->at<T>(L.w_lm) + (size_t)c0 * d, d, D, w, d, el, st);
+      ProfScope ps(ctx, ALR_PROF_LM_FINALIZE, st);
+      label_panel_kernel<<<D, 256, 0, st>>>(el.out, w, c0, el.part, w / 64, urow,
+                                            ctx->at<int>(L.i_ctok), state);
+      ALR_LAUNCHED(ctx, "corpus label panel");
+    }
+    const long items = (long)n * block * 8;
+    label_expand_kernel<<<(unsigned)((items + 255) / 256), 256, 0, st>>>(
+        state, ctx->at<int>(L.i_uidx), ctx->at<int>(L.i_perm), ctx->at<int>(L.i_atok),
+        ctx->at<int>(L.i_apos), ctx->at<int>(L.i_alen), n, block, out.tokens, out.top_ids,
+        out.top_logp, out.tail, corpus_logp);
+    ALR_LAUNCHED(ctx, "corpus label expansion");
+  }
+  for (int s = 0; out.logprobs && s < block; ++s) {
     corpus_rows_kernel<T><<<n, 256, 0, st>>>(
         ctx->at<T>(L.xnorm), ctx->at<T>(L.hf_store), ctx->at<int>(L.i_atok),
         ctx->at<int>(L.i_apos), ctx->at<int>(L.i_alen), ctx->at<int>(L.i_ctok), s, d,
@@ -1037,12 +1094,6 @@ alr_status corpus_impl(alr_ctx* ctx, int n, int block, const LabelDst& out, floa
       ctx->at<int>(L.i_alen), ctx->at<int>(L.i_ctok), corpus_logp, out.tokens, n, block,
       gate_soft, gate_hard);
   ALR_LAUNCHED(ctx, "erase gates");
-  return ALR_OK;
-}
-
-alr_status upload(alr_ctx* ctx, void* dst, const void* src, size_t bytes, hipStream_t st) {
-  if (bytes == 0) return ALR_OK;
-  ALR_HIP(ctx, hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, st));
   return ALR_OK;
 }
 
@@ -1530,6 +1581,17 @@ alr_status prepare_anchors(alr_ctx* ctx, int32_t n_anchor, const int32_t* anchor
       for (int r = 0; r < n; ++r) sq_sorted[r] = anchor_seq[order[r]];
       plan_decode(c, ctx->n_cu, n, sq_sorted.data(), apos, ctx->seq_off.data(),
                   ctx->seq_vcol.data(), ctx->h_dwork, ctx->h_groups, ctx->h_grprow);
+    }
+  }
+  if (!rollout) {
+    // anchors are sorted, so the positions a sequence's slots cover rise
+    ctx->h_urow.clear();
+    int next = 0;  // first token row not yet listed
+    for (int r = 0; r < n; ++r) {
+      const int end = atok[r] - apos[r] + alen[r];
+      for (int t = std::max(next, atok[r]); t < std::min(end, atok[r] + block); ++t)
+        ctx->h_urow.push_back(t + 1 < end ? t : -1 - t);
+      next = std::max(next, std::min(end, atok[r] + block));
     }
   }
   // per sorted row: its first partial row (kv head 0, chunk 0) and its group's chunk count

@@ -207,3 +207,43 @@ def test_ira_assemble_matches_oracle():
             eng.ira_assemble(tok, ids, tl, tt, [0], [bad])
         assert e.value.status == 2
     eng.close()
+
+
+@pytest.mark.parametrize("dtype,vocab,block,max_anchors", [
+    ("f32", 64, 6, 6),        # one 64-column group per row, narrower than a panel
+    ("f32", 512, 6, 6),       # panels of single groups
+    ("bf16", 512, 16, 6),     # panels of 64 columns, fewer columns than 8 groups
+    ("bf16", 4160, 16, 6),    # 256-column panels and a ragged last one
+    ("bf16", 4160, 5, 300),   # one panel
+])
+def test_corpus_labels_panels_match_rows(dtype, vocab, block, max_anchors):
+    """Labels formed once per position, panel by panel, against the per-slot path that also
+    writes the log-prob rows (overlapping anchors, duplicates, slots past the end, given rows)."""
+    base = W.get("tiny_fp32")
+    w = W.scaled(base, "labels_panels", vocab=vocab, dtype=dtype, n_seq=2, seq_len=70,
+                 anchor_hi=69, block=block)
+    rng = np.random.default_rng(vocab + block)
+    mask = np.zeros(w.n_tokens, np.uint8)
+    mask[30:36] = 1
+    rows = rng.standard_normal((w.n_tokens, w.shape.d_model)).astype(np.float32)
+    rows = W.f32_to_bf16_bits(rows) if dtype == "bf16" else rows
+    inp = W.Inputs(w, W.random_weights(w.shape, 5, scale=0.1), W.random_tokens(vocab, (2, 70), 6),
+                   np.array([1, 0, 1, 0, 0, 1], np.int32),
+                   np.array([69, 28, 3, 31, 31, 64], np.int32), rows, mask)
+    eng = make_engine(inp, max_anchors=max_anchors)
+    prefill(eng, inp)
+    a = eng.corpus_labels(inp.anchor_seq, inp.anchor_pos, block)
+    b = eng.corpus_labels(inp.anchor_seq, inp.anchor_pos, block, want_logprobs=True)
+    torch.cuda.synchronize()
+    for k in ("argmax", "top_ids", "gate_hard"):
+        assert torch.equal(a[k], b[k]), k
+    for k in ("top_logp", "tail", "corpus_logp", "gate_soft"):
+        # fp32 sums over the vocabulary in another grouping: a few ulp of the log-sum-exp
+        np.testing.assert_allclose(_np(a[k]), _np(b[k]), rtol=4e-6, atol=4e-6, err_msg=k)
+    lpn = _np(b["logprobs"]).reshape(-1, vocab)
+    ok = np.isfinite(lpn).all(1)
+    mask_top = np.ones((ok.sum(), vocab), bool)
+    np.put_along_axis(mask_top, _np(a["top_ids"]).reshape(-1, 8)[ok].astype(np.int64), False, 1)
+    tail = np.where(mask_top, np.exp(lpn[ok].astype(np.float64)), 0).sum(-1)
+    np.testing.assert_allclose(_np(a["tail"]).reshape(-1)[ok], tail, rtol=1e-5, atol=1e-7)
+    eng.close()
