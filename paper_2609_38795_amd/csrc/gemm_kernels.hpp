@@ -4,7 +4,8 @@
 // 256x256 ping-pong kernel over register-staged BK = 64 tiles, run
 // persistently (gemm_bf16_pp64p_kernel; gemm_bf16_pp64_kernel is the same
 // schedule one tile per workgroup, used for split-K); GEMMs with fewer than
-// 256 such tiles use the LDS-staged gemm_bf16_kernel at 128x128 or 64x128.
+// 256 such tiles use the LDS-staged gemm_bf16_kernel at 128x128 or 64x128, and
+// products of few rows gemm_bf16_ring_kernel.
 // fp32 path: FMA, 64x64x16 tile.  Both hand the epilogue *pairs* of outputs:
 // the value at column c and the one at column c+32, where c lies in the low
 // half of a 64-column group.
@@ -168,19 +169,21 @@ struct EpiQKV {
       *(f32x4*)p = x;
     }
   }
-  // The 16 rows of a lane's 32-row block (row of index t: rb + 8 (t >> 2) +
+  // NR (4 or 16) rows of a lane's 32-row block (row of index t: rb + 8 (t >> 2) +
   // (t & 3); rows >= M are skipped) of columns c and c+32.  Every load the
   // rows need (positions, then cos/sin, or the V^T columns) is issued before
   // any store, so the block costs two memory round trips rather than one per
   // row.  Four consecutive, 4-aligned columns of the transposed V cache go out
   // as one 8-byte store per column (bf16).
-  __device__ __forceinline__ void rows16(int rb, int M, int c, const float* lo,
-                                         const float* hi) const {
+  static constexpr bool by_rows = true;
+  template <int NR>
+  __device__ __forceinline__ void rows(int rb, int M, int c, const float* lo,
+                                       const float* hi) const {
     const int half = hd >> 1;
     const int qd = H * hd, kd = G * hd;
-    int r[16];
+    int r[NR];
 #pragma unroll
-    for (int t = 0; t < 16; ++t) r[t] = rb + 8 * (t >> 2) + (t & 3);
+    for (int t = 0; t < NR; ++t) r[t] = rb + 8 * (t >> 2) + (t & 3);
     if (c < qd + kd) {
       OutT* base;
       long rs;
@@ -197,12 +200,12 @@ struct EpiQKV {
       const int f = 32 * (cl >> 6) + (cl & 63);
       const int head = f / half, i = f - head * half;
       const int axis = (i < sec0) ? 0 : ((i < sec01) ? 1 : 2);
-      int pp[16];
+      int pp[NR];
 #pragma unroll
-      for (int t = 0; t < 16; ++t) pp[t] = pos[3 * min(r[t], M - 1) + axis];
-      float cs[16], sn[16];
+      for (int t = 0; t < NR; ++t) pp[t] = pos[3 * min(r[t], M - 1) + axis];
+      float cs[NR], sn[NR];
 #pragma unroll
-      for (int t = 0; t < 16; ++t) {
+      for (int t = 0; t < NR; ++t) {
         const long o = (long)(pp[t] + pos_add) * half + i;
         cs[t] = cosT[o];
         sn[t] = sinT[o];
@@ -212,14 +215,14 @@ struct EpiQKV {
       // writes row r at i, i+1 and the odd lane row r+1: one store of two
       // elements per half instead of two single-element stores.
       const int odd = c & 1;
-      float a[16], b[16];
+      float a[NR], b[NR];
 #pragma unroll
-      for (int t = 0; t < 16; ++t) {
+      for (int t = 0; t < NR; ++t) {
         a[t] = rope_a(lo[t], hi[t], cs[t], sn[t]);
         b[t] = rope_b(lo[t], hi[t], cs[t], sn[t]);
       }
 #pragma unroll
-      for (int t = 0; t < 16; t += 2) {
+      for (int t = 0; t < NR; t += 2) {
         const f32x2 pa = pair_rows(odd, a[t], a[t + 1]), pb = pair_rows(odd, b[t], b[t + 1]);
         const int rr = r[t] + odd;
         if (rr < M) {
@@ -230,11 +233,11 @@ struct EpiQKV {
       }
     } else if (vt_col) {
       const long cl = c - qd - kd;
-      int col[16];
+      int col[NR];
 #pragma unroll
-      for (int t = 0; t < 16; ++t) col[t] = vt_col[min(r[t], M - 1)];
+      for (int t = 0; t < NR; ++t) col[t] = vt_col[min(r[t], M - 1)];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
+      for (int g = 0; g < NR / 4; ++g) {
         const int t0 = 4 * g;
         if constexpr (std::is_same<OutT, bf16>::value) {
           if (r[t0 + 3] < M && col[t0 + 3] == col[t0] + 3 && (col[t0] & 3) == 0) {
@@ -259,7 +262,7 @@ struct EpiQKV {
     } else {
       const int cl = c - qd - kd;
 #pragma unroll
-      for (int t = 0; t < 16; ++t)
+      for (int t = 0; t < NR; ++t)
         if (r[t] < M) {
           OutT* dst = v + (long)r[t] * kv_rs;
           Elt<OutT>::st(dst + cl, lo[t]);
@@ -270,14 +273,14 @@ struct EpiQKV {
 };
 
 // Epilogues that read memory, or that write two columns per access, define
-// rows16(): a lane's 16 rows of a 32-row block at once, all loads before all
-// stores (the compiler cannot prove that a later row's load does not alias an
-// earlier row's store, so element-wise calls would wait for one load round
-// trip per row).
+// rows<NR>(): a lane's 16 rows of a 32-row block (or four of them) at once, all
+// loads before all stores (the compiler cannot prove that a later row's load
+// does not alias an earlier row's store, so element-wise calls would wait for
+// one load round trip per row).
 template <class Epi, class = void>
-struct has_rows16 : std::false_type {};
+struct has_rows : std::false_type {};
 template <class Epi>
-struct has_rows16<Epi, decltype((void)&Epi::rows16)> : std::true_type {};
+struct has_rows<Epi, decltype((void)Epi::by_rows)> : std::true_type {};
 
 // Residual add into the fp32 stream, optionally capturing the new value as a
 // feature row: feat + (perm ? perm[row] : row) * feat_rs.
@@ -305,19 +308,21 @@ struct EpiResid {
   // leave the CU's matrix cores idle).  With feature rows (and their
   // permutation indices) two halves of 8 rows bound the registers the
   // epilogue needs inside a persistent kernel.
-  __device__ __forceinline__ void rows16(int rb, int M, int c, const float* lo,
-                                         const float* hi) const {
+  static constexpr bool by_rows = true;
+  template <int NR>
+  __device__ __forceinline__ void rows(int rb, int M, int c, const float* lo,
+                                       const float* hi) const {
     if (!feat) {
-      float a[16], b[16];
+      float a[NR], b[NR];
 #pragma unroll
-      for (int t = 0; t < 16; ++t) {
+      for (int t = 0; t < NR; ++t) {
         const int rc = min(rb + 8 * (t >> 2) + (t & 3), M - 1);
         const float* p = h + (long)rc * ld + c;
         a[t] = p[0];
         b[t] = p[32];
       }
 #pragma unroll
-      for (int t = 0; t < 16; ++t) {
+      for (int t = 0; t < NR; ++t) {
         const int r = rb + 8 * (t >> 2) + (t & 3);
         if (r < M) {
           float* p = h + (long)r * ld + c;
@@ -327,13 +332,14 @@ struct EpiResid {
       }
       return;
     }
+    constexpr int HR = NR < 8 ? NR : 8;
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      int fr[8];
-      float a[8], b[8];
+    for (int half = 0; half < NR / HR; ++half) {
+      int fr[HR];
+      float a[HR], b[HR];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int t = 8 * half + u;
+      for (int u = 0; u < HR; ++u) {
+        const int t = HR * half + u;
         const int r = rb + 8 * (t >> 2) + (t & 3), rc = min(r, M - 1);
         const float* p = h + (long)rc * ld + c;
         a[u] = p[0];
@@ -341,8 +347,8 @@ struct EpiResid {
         fr[u] = perm ? perm[rc] : r;
       }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int t = 8 * half + u;
+      for (int u = 0; u < HR; ++u) {
+        const int t = HR * half + u;
         const int r = rb + 8 * (t >> 2) + (t & 3);
         if (r < M) {
           a[u] += lo[t];
@@ -378,15 +384,17 @@ struct EpiSwiGLU {
   // Rows rb + 8 q + e of one column, written two columns per store after the
   // lane-pair exchange (pair_rows); the pair's first output column is even
   // because d_ffn is a multiple of 64.
-  __device__ __forceinline__ void rows16(int rb, int M, int c, const float* lo,
-                                         const float* hi) const {
+  static constexpr bool by_rows = true;
+  template <int NR>
+  __device__ __forceinline__ void rows(int rb, int M, int c, const float* lo,
+                                       const float* hi) const {
     const int odd = c & 1;
     const int col = (c >> 6) * 32 + (c & 63) - odd;
-    float y[16];
+    float y[NR];
 #pragma unroll
-    for (int t = 0; t < 16; ++t) y[t] = act(lo[t], hi[t]);
+    for (int t = 0; t < NR; ++t) y[t] = act(lo[t], hi[t]);
 #pragma unroll
-    for (int t = 0; t < 16; t += 2) {
+    for (int t = 0; t < NR; t += 2) {
       const f32x2 x = pair_rows(odd, y[t], y[t + 1]);
       const int r = rb + 8 * (t >> 2) + (t & 3) + odd;
       if (r < M) {
@@ -441,32 +449,34 @@ struct EpiLogits {
       if ((threadIdx.x & 31) == 0) part[(long)row * part_ld + (c >> 6)] = q;
     }
   }
-  __device__ __forceinline__ void rows16(int rb, int M, int c, const float* lo,
-                                         const float* hi) const {
-    int rr[16];
+  static constexpr bool by_rows = true;
+  template <int NR>
+  __device__ __forceinline__ void rows(int rb, int M, int c, const float* lo,
+                                       const float* hi) const {
+    int rr[NR];
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
+    for (int t = 0; t < NR; ++t) {
       const int r = rb + 8 * (t >> 2) + (t & 3);
       rr[t] = perm ? perm[min(r, M - 1)] : r;
     }
 #pragma unroll
-    for (int t = 0; t < 16; ++t)
+    for (int t = 0; t < NR; ++t)
       if (rb + 8 * (t >> 2) + (t & 3) < M) {
         float* p = out + (long)rr[t] * rs + c;
         p[0] = lo[t];
         p[32] = hi[t];
       }
     if (part) {
-      // all 16 rows reduced over the half-wave; lane lr < 16 then stores row t = lr
+      // all rows reduced over the half-wave; lane lr < NR then stores row t = lr
       const int lr = threadIdx.x & 31;
       LogitPart mine = {0.f, 0.f};
 #pragma unroll
-      for (int t = 0; t < 16; ++t) {
+      for (int t = 0; t < NR; ++t) {
         const LogitPart q = half_wave_part(lo[t], hi[t]);
         if (lr == t) mine = q;
       }
       const int r = rb + 8 * (lr >> 2) + (lr & 3);
-      if (lr < 16 && r < M) part[(long)r * part_ld + (c >> 6)] = mine;
+      if (lr < NR && r < M) part[(long)r * part_ld + (c >> 6)] = mine;
     }
   }
 };
@@ -475,7 +485,7 @@ struct EpiLogits {
 // output is (row0, col0): lane (lr, lh) of block (mi, nj) holds rows row0 +
 // 32 mi + 8 q + 4 lh + e (q, e = 0..3; register 4 q + e) of columns col0 +
 // 64 nj + lr and that + 32 (accumulators 2 nj and 2 nj + 1).  Epilogues with
-// a rows16() form get those 16 rows in one call.
+// a rows() form get those 16 rows in one call.
 template <int MI, int NI, class Epi>
 __device__ __forceinline__ void gemm_store_tile(const Epi& epi, const f32x16 (&acc)[MI][NI],
                                                 int row0, int col0, int M, int N) {
@@ -486,7 +496,7 @@ __device__ __forceinline__ void gemm_store_tile(const Epi& epi, const f32x16 (&a
     if (col < N) {
 #pragma unroll
       for (int mi = 0; mi < MI; ++mi) {
-        if constexpr (has_rows16<Epi>::value) {
+        if constexpr (has_rows<Epi>::value) {
           const int rb = row0 + mi * 32 + 4 * lh;
           if (rb < M) {
             float lo[16], hi[16];
@@ -495,7 +505,7 @@ __device__ __forceinline__ void gemm_store_tile(const Epi& epi, const f32x16 (&a
               lo[t] = acc[mi][2 * nj][t];
               hi[t] = acc[mi][2 * nj + 1][t];
             }
-            epi.rows16(rb, M, col, lo, hi);
+            epi.template rows<16>(rb, M, col, lo, hi);
           }
         } else {
 #pragma unroll
@@ -1068,6 +1078,156 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_pp64p_kernel(
     if (next < ntiles) offsets(next, gnxt);
   }
   if (grp == 0) __builtin_amdgcn_s_barrier();
+}
+
+// ------------------------------------------------------------------ bf16 MFMA GEMM, few rows
+//
+// For products whose rows fit one or two 128-row tiles: the weights are read
+// once and dominate, so what counts is how many of their bytes are in flight.
+// Tile BM x BN over K steps of 64; the operands go from global memory straight
+// into a ring of ST LDS stages (copy_1k; wave w issues blocks w, w + NW, ... of
+// the stage's 1 KB blocks, 8 rows of 128 bytes each, XOR-swizzled as swz<64>),
+// ST - 1 stages ahead and without staging registers.  One barrier per step: it
+// publishes the stage whose copies every wave has just waited for, and it says
+// that the stage read in the step before is free, which is then refilled.
+//   WGM x WGN waves split the tile; where the tile has fewer 32 x 64 blocks than
+// waves, WGK of them share a block and take the step's four 16-element slices
+// among themselves, summed in wave order through LDS before the epilogue.
+//   Workgroup b runs on XCD b % 8; units (column tile, K slice) are dealt to the
+// XCDs in turn, and the row tiles of a unit follow each other on its XCD, so
+// they share the unit's weights in that L2.  With splits > 1 unit u is K slice
+// u % splits (of K columns) of column tile u / splits.
+template <int N>
+__device__ __forceinline__ void ring_wait() {  // vmcnt(N), lgkmcnt(0)
+  static_assert(N >= 0 && N < 64, "vmcnt has 6 bits");
+  __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4));
+}
+
+template <int TAG, int BM, int BN, int WGM, int WGN, int WGK, int ST, class Epi>
+__global__ __launch_bounds__(64 * WGM * WGN * WGK) void gemm_bf16_ring_kernel(
+    const bf16* __restrict__ A, int lda, const bf16* __restrict__ W, int ldw, int M, int N, int K,
+    int tiles_m, int tiles_n, Epi epi, int splits) {
+  constexpr int NW = WGM * WGN * WGK, BK = 64, KS = BK / 16 / WGK;
+  constexpr int WTM = BM / WGM, WTN = BN / WGN, MI = WTM / 32, NI = WTN / 32;
+  static_assert(WTN % 64 == 0 && WTM % 32 == 0 && KS >= 1, "wave tile");
+  static_assert(WGK == 1 || (MI == 1 && NI == 2), "waves share a single 32 x 64 block");
+  constexpr int NBLK = (BM + BN) / 8, CPW = NBLK / NW, STAGE = (BM + BN) * BK;
+  static_assert(CPW * NW == NBLK, "a stage splits evenly over the waves");
+  static_assert(WGK == 1 || ST * STAGE * 2 >= NW * 64 * 32 * 4, "the sums fit the ring");
+  __shared__ __attribute__((aligned(1024))) bf16 smem[ST * STAGE];
+
+  const int unit = (int)(blockIdx.x / (8 * tiles_m)) * 8 + (int)(blockIdx.x & 7);
+  const int tm = (int)(blockIdx.x >> 3) % tiles_m;
+  if (unit >= tiles_n * splits) return;  // uniform over the workgroup
+  const int sl = unit % splits, m0 = tm * BM, n0 = unit / splits * BN;
+  A += (long)sl * K;
+  W += (long)sl * K;
+  if constexpr (has_set_split<Epi>::value) epi.set_split(sl);
+
+  const int lane = threadIdx.x & 63, lr = lane & 31, lh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wk = wave % WGK, wn = wave / WGK % WGN, wm = wave / (WGK * WGN);
+  uint32_t goff[CPW];
+#pragma unroll
+  for (int j = 0; j < CPW; ++j) {
+    const int r = 8 * (j * NW + wave) + (lane >> 3);
+    const int c = (lane & 7) ^ ((r & 7) ^ ((r >> 3) & 1));
+    goff[j] = (uint32_t)(((r < BM ? (long)min(m0 + r, M - 1) * lda
+                                  : (long)min(n0 + r - BM, N - 1) * ldw) + c * 8) * 2);
+  }
+  const uint32_t lds0 = lds_byte_addr(smem) + wave * 1024;
+  // Units start their walk over K at different steps: rows are a power of two
+  // apart in most models, so walking in step would have every workgroup read the
+  // same few memory channels at a time (M = 16, N = 28672, K = 4096: 45 -> 42 us,
+  // 5.2 -> 5.6 TB/s).
+  const int nk = K / BK, rot = unit % nk;
+  auto fetch = [&](int step, int slot) {
+    step += rot;
+    if (step >= nk) step -= nk;
+    const bf16 *a = A + (long)step * BK, *w = W + (long)step * BK;
+#pragma unroll
+    for (int j = 0; j < CPW; ++j)
+      copy_1k(lds0 + (uint32_t)(slot * STAGE * 2 + j * NW * 1024), goff[j],
+              8 * (j * NW + wave) < BM ? a : w);
+  };
+#pragma unroll
+  for (int s = 0; s < ST - 1; ++s)
+    if (s < nk) fetch(s, s);
+
+  f32x16 acc[MI][NI];
+#pragma unroll
+  for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
+
+  int slot = 0;
+  for (int kt = 0; kt < nk; ++kt) {
+    __builtin_amdgcn_sched_barrier(0);
+    if (kt + ST - 2 < nk)
+      ring_wait<CPW * (ST - 2)>();
+    else
+      ring_wait<0>();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    const bf16* As = smem + slot * STAGE;
+    if (kt + ST - 1 < nk) fetch(kt + ST - 1, slot == 0 ? ST - 1 : slot - 1);
+    slot = slot + 1 == ST ? 0 : slot + 1;
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      GemmFrag<MI, NI> f;
+      gemm_frag_load<BK, MI, NI, WTM, WTN>(f, As, As + BM * BK, wm, wn, wk * KS + k);
+      gemm_frag_mma<MI, NI>(f, acc);
+    }
+  }
+
+  if constexpr (WGK == 1) {
+    gemm_store_tile<MI, NI>(epi, acc, m0 + wm * WTM, n0 + wn * WTN, M, N);
+  } else {
+    // wave wk takes the block's row runs 8 q + 4 lh .. + 3 of q = wk NQ .. wk NQ + NQ - 1
+    constexpr int NQ = 4 / WGK;
+    f32x4* red = (f32x4*)smem;  // [block][wk][q][half][lane]
+    const int blk = wm * WGN + wn;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = acc[0][h][4 * q + e];
+        red[(((blk * WGK + wk) * 4 + q) * 2 + h) * 64 + lane] = v;
+      }
+    __syncthreads();
+    const int col = n0 + wn * WTN + lr;
+    if (col >= N) return;
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      const int q = wk * NQ + i, rb = m0 + wm * WTM + 8 * q + 4 * lh;
+      float x[2][4];
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[h][e] = 0.f;
+#pragma unroll
+      for (int k = 0; k < WGK; ++k)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const f32x4 v = red[(((blk * WGK + k) * 4 + q) * 2 + h) * 64 + lane];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[h][e] += v[e];
+        }
+      if (rb >= M) continue;
+      if constexpr (has_rows<Epi>::value) {
+        epi.template rows<4>(rb, M, col, x[0], x[1]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (rb + e < M) epi(rb + e, col, x[0][e], x[1][e]);
+      }
+    }
+  }
 }
 
 // ------------------------------------------------------------------ fp32 FMA GEMM

@@ -156,6 +156,9 @@ alr_status check_operand_sizes(const alr_config& c, const alr_limits& lim, char*
   return ALR_OK;
 }
 
+// Products of at most this many rows run on the ring kernels (pick_ring).
+constexpr int RING_MAX_ROWS = 256;
+
 int anchor_group(const alr_config& c) { return std::max(1, 128 / (c.n_heads / c.n_kv_heads)); }
 
 bool mfma_attn(const alr_config& c) {
@@ -253,8 +256,10 @@ size_t compute_layout(const alr_config& c, const alr_limits& lim, Layout& L) {
   L.i_rowinfo = take(NA * 2 * 4);
   L.part_o = take(L.max_dwork * 128 * hd * 2);  // fp16, normalised by the chunk sum
   L.part_ml = take(L.max_dwork * 128 * 2 * 4);
-  // split-K partial sums of the rollout GEMMs: up to 4 slices of [anchors, N] fp32
-  L.splitk_bytes = 4 * NA * std::max(qd + 2 * kvd, d) * 4;
+  // split-K partial sums of the rollout GEMMs: up to 4 slices of [anchors, N] fp32,
+  // and up to 8 where there are few rows
+  L.splitk_bytes = std::max(4 * NA, 8 * std::min<size_t>(NA, RING_MAX_ROWS)) *
+                   std::max(qd + 2 * kvd, d) * 4;
   L.splitk = take(L.splitk_bytes);
   L.total = off;
   return off;
@@ -441,6 +446,10 @@ void launch_splitk_reduce(const float* part, long sstride, int S, int M, int N, 
       splitk_reduce4_kernel<Epi, 4><<<nb4, 256, 0, st>>>(part, sstride, M, N, epi);
       return;
     }
+    if (S == 8) {
+      splitk_reduce4_kernel<Epi, 8><<<nb4, 256, 0, st>>>(part, sstride, M, N, epi);
+      return;
+    }
   }
   const long thr = (long)M * (N / 64) * 32;
   const unsigned nb = (unsigned)((thr + 255) / 256);
@@ -459,7 +468,7 @@ void launch_splitk_reduce(const float* part, long sstride, int S, int M, int N, 
 template <typename T>
 bool launch_splitk_resid_norm(alr_ctx* ctx, int S, int M, int N, const EpiResid& er, const T* g,
                               T* out, hipStream_t st) {
-  if (er.ld != N || N % 4 != 0 || N > 8192 || (S != 2 && S != 4)) return false;
+  if (er.ld != N || N % 4 != 0 || N > 8192 || (S != 2 && S != 4 && S != 8)) return false;
   const int ch = (N + 1023) / 1024;
   const float eps = ctx->cfg.rms_eps;
   const float* part = ctx->splitk_buf;
@@ -469,11 +478,76 @@ bool launch_splitk_resid_norm(alr_ctx* ctx, int S, int M, int N, const EpiResid&
                                                           er.perm, g, out, N, eps)
   if (S == 2) {
     if (ch <= 1) ALR_RN(2, 1); else if (ch <= 2) ALR_RN(2, 2); else if (ch <= 4) ALR_RN(2, 4); else ALR_RN(2, 8);
-  } else {
+  } else if (S == 4) {
     if (ch <= 1) ALR_RN(4, 1); else if (ch <= 2) ALR_RN(4, 2); else if (ch <= 4) ALR_RN(4, 4); else ALR_RN(4, 8);
+  } else {
+    // 8 slices of more than 4096 columns would not fit the registers
+    if (ch <= 1) ALR_RN(8, 1); else if (ch <= 2) ALR_RN(8, 2); else if (ch <= 4) ALR_RN(8, 4); else return false;
   }
 #undef ALR_RN
   return true;
+}
+
+// Kernel and K slices of a product of few rows (M <= RING_MAX_ROWS).  Such a
+// product reads its weights once whatever the choice; beyond that a kernel
+// takes about `step_us` per K step of a workgroup (barrier, operand reads and
+// the copies the step waits for; measured over K = 1024 .. 18944), workgroups
+// beyond one per CU queue behind the first, and slices cost the fp32 partials
+// they write and re-read plus a second launch unless that is the reduce which
+// carries the following RMSNorm.  The choice minimises the sum:
+//   rows   tile      us/step   e.g. N = 6144, K = 4096 (unsplit 64x128 tiles: 33)
+//   <= 32   32 x 64    0.26    2 slices 11.8 us
+//   <= 64   64 x 64    0.34    4 slices 13.4 us
+//   else   128 x 64    0.47    2 slices 18.4 us (M = 128)
+//          128 x 128   0.57    4 slices 15.2 us (M = 128)
+struct RingPlan {
+  int bm, bn, splits;
+};
+RingPlan pick_ring(int M, int N, int K, int n_cu, size_t split_bytes, bool norm_follows) {
+  struct Kern {
+    int bm, bn;
+    float step_us;
+  };
+  static const Kern kerns[] = {{32, 64, 0.26f}, {64, 64, 0.34f}, {128, 64, 0.47f}, {128, 128, 0.57f}};
+  RingPlan best{0, 0, 0};
+  float best_us = 0.f;
+  for (const Kern& k : kerns) {
+    if (M <= 32 ? k.bm != 32 : (M <= 64 ? k.bm != 64 : k.bm != 128)) continue;
+    const int t = ((M + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn);
+    for (int S = 1; S <= 8; S *= 2) {
+      if (S > 1 && ((long)t * S > n_cu || K % (64 * S) != 0 || K / S < 256 ||
+                    (size_t)S * M * N * 4 > split_bytes || (S == 8 && N > 4096)))
+        continue;
+      const int rounds = (t * S + n_cu - 1) / n_cu;
+      float us = (float)(K / 64 / S) * k.step_us * rounds;
+      if (S > 1) us += 2e-6f * S * M * N + (norm_follows ? 0.f : 5.f);
+      if (best.splits == 0 || us < best_us) {
+        best = RingPlan{k.bm, k.bn, S};
+        best_us = us;
+      }
+    }
+  }
+  return best;
+}
+
+template <int TAG, class Epi>
+void launch_ring(const RingPlan& p, const bf16* A, int lda, const bf16* W, int ldw, int M, int N,
+                 int K, const Epi& epi, hipStream_t st) {
+  const int tm = (M + p.bm - 1) / p.bm, tn = (N + p.bn - 1) / p.bn;
+  const unsigned grid = (unsigned)((tn * p.splits + 7) / 8 * 8 * tm);
+  const int Ks = K / p.splits;
+#define ALR_RING(BM_, BN_, WGM_, WGN_, WGK_, ST_)                                  \
+  gemm_bf16_ring_kernel<TAG, BM_, BN_, WGM_, WGN_, WGK_, ST_, Epi>                 \
+      <<<grid, 64 * WGM_ * WGN_ * WGK_, 0, st>>>(A, lda, W, ldw, M, N, Ks, tm, tn, epi, p.splits)
+  if (p.bm == 32)
+    ALR_RING(32, 64, 1, 1, 4, 5);
+  else if (p.bm == 64)
+    ALR_RING(64, 64, 2, 1, 2, 4);
+  else if (p.bn == 64)
+    ALR_RING(128, 64, 4, 1, 1, 3);
+  else
+    ALR_RING(128, 128, 4, 2, 1, 4);
+#undef ALR_RING
 }
 
 // norm_g / norm_out / normed: the RMSNorm that follows a residual update
@@ -506,6 +580,25 @@ void launch_gemm(alr_ctx* ctx, const T* A, int lda, const T* W, int ldw, int M, 
     // tile; a split-K reduce hands it columns in another arrangement
     bool epi_whole_k = false;
     if constexpr (std::is_same<Epi, EpiLogits>::value) epi_whole_k = epi.part != nullptr;
+    if (cfg == 0 && M <= RING_MAX_ROWS) {
+      const bool may_split = ctx->splitk_buf != nullptr && !epi_whole_k;
+      const RingPlan p = pick_ring(M, N, K, ctx->n_cu, may_split ? ctx->splitk_bytes : 0,
+                                   norm_out != nullptr);
+      if (p.splits == 1) {
+        launch_ring<TAG>(p, A, lda, W, ldw, M, N, K, epi, st);
+        return;
+      }
+      launch_ring<TAG>(p, A, lda, W, ldw, M, N, K, EpiPartial{ctx->splitk_buf, (long)M * N, N}, st);
+      if constexpr (std::is_same<Epi, EpiResid>::value) {
+        if (norm_out && normed &&
+            launch_splitk_resid_norm<T>(ctx, p.splits, M, N, epi, norm_g, norm_out, st)) {
+          *normed = true;
+          return;
+        }
+      }
+      launch_splitk_reduce(ctx->splitk_buf, (long)M * N, p.splits, M, N, epi, st);
+      return;
+    }
     // Few rows (the rollout of a small batch): when even split-K leaves more
     // than half the CUs without a 256x256 tile, 64x128 tiles split over K
     // (slices of >= 256 and a multiple of 64) spread the work over more CUs.
@@ -565,8 +658,7 @@ void launch_gemm(alr_ctx* ctx, const T* A, int lda, const T* W, int ldw, int M, 
       if (cfg == 18) cfg = 0;
     }
     if (cfg == 0)
-      cfg = tiles(256, 256) >= 256 ? ((K % 64) == 0 ? 19 : 4) : (tiles(128, 128) >= 256 ? 2 : 3);
-    if ((cfg == 17 || cfg == 19) && (K % 64) != 0) cfg = 4;
+      cfg = tiles(256, 256) >= 256 ? 19 : (tiles(128, 128) >= 256 ? 2 : 3);  // K is a multiple of 64
     const bool k64 = (K % 128) == 0;
     const int bm = (cfg == 1 || cfg == 4 || cfg == 5 || cfg >= 17) ? 256 : (cfg == 3 ? 64 : 128);
     const int bn = (cfg == 4 || cfg == 5 || cfg >= 17) ? 256 : 128;
@@ -575,17 +667,22 @@ void launch_gemm(alr_ctx* ctx, const T* A, int lda, const T* W, int ldw, int M, 
 #define ALR_GEMM(BM_, BN_, WGM_, WGN_, BK_, OCC_)                                      \
   gemm_bf16_kernel<TAG, BM_, BN_, WGM_, WGN_, BK_, OCC_, Epi>                          \
       <<<nb, 64 * WGM_ * WGN_, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi)
+    if constexpr (TAG == 0) {  // the debug hook's variants
+      switch (cfg) {
+        case 17:
+          gemm_bf16_pp64_kernel<TAG, Epi><<<nb, 512, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
+          return;
+        case 5: if (k64) ALR_GEMM(256, 256, 2, 2, 64, 1); else ALR_GEMM(256, 256, 2, 2, 32, 1); return;
+        case 4: if (k64) ALR_GEMM(256, 256, 2, 4, 64, 1); else ALR_GEMM(256, 256, 2, 4, 32, 1); return;
+        case 1: if (k64) ALR_GEMM(256, 128, 2, 2, 64, 1); else ALR_GEMM(256, 128, 2, 2, 32, 1); return;
+        default: break;
+      }
+    }
     switch (cfg) {
-      case 17:
-        gemm_bf16_pp64_kernel<TAG, Epi><<<nb, 512, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
-        break;
       case 19:
         gemm_bf16_pp64p_kernel<TAG, Epi>
             <<<std::min(nb, ctx->n_cu), 512, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
         break;
-      case 5: if (k64) ALR_GEMM(256, 256, 2, 2, 64, 1); else ALR_GEMM(256, 256, 2, 2, 32, 1); break;
-      case 4: if (k64) ALR_GEMM(256, 256, 2, 4, 64, 1); else ALR_GEMM(256, 256, 2, 4, 32, 1); break;
-      case 1: if (k64) ALR_GEMM(256, 128, 2, 2, 64, 1); else ALR_GEMM(256, 128, 2, 2, 32, 1); break;
       case 2: if (k64) ALR_GEMM(128, 128, 2, 2, 64, 2); else ALR_GEMM(128, 128, 2, 2, 32, 2); break;
       default: if (k64) ALR_GEMM(64, 128, 2, 2, 64, 2); else ALR_GEMM(64, 128, 2, 2, 32, 4); break;
     }

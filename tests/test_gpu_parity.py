@@ -47,6 +47,45 @@ def test_gemm_kernel(dtype, tile, M, N, K):
     assert err <= 2e-5 * np.sqrt(K) * 4, err
 
 
+@pytest.mark.parametrize("M", [1, 31, 32, 33, 64, 65, 128, 129, 256])
+@pytest.mark.parametrize("N,K", [(64, 64), (192, 192), (320, 1536), (8256, 512)])
+def test_gemm_few_rows(M, N, K):
+    """The ring kernels at the edges of their row tiles, with fewer K steps than ring stages,
+    column tiles that end mid-tile, and more column tiles than CUs, against float64."""
+    _print(f"gemm few rows {M}x{N}x{K}")
+    rng = np.random.default_rng(M + N + K)
+    a = O.bf16_round(rng.standard_normal((M, K)).astype(np.float32))
+    w = O.bf16_round(rng.standard_normal((N, K)).astype(np.float32))
+    ta, tw = (torch.from_numpy(x).to("cuda").to(torch.bfloat16) for x in (a, w))
+    c = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    binding.debug_gemm(binding.ALR_BF16, ta, tw, c)
+    err = np.abs(c.cpu().numpy() - a.astype(np.float64) @ w.astype(np.float64).T).max()
+    assert err <= 2e-5 * np.sqrt(K) * 4, err
+
+
+def test_rollout_batches_agree():
+    """The first n anchors rolled out alone (ring kernels, each row tile, split and unsplit)
+    against the same anchors in a batch of 257 (the tiled kernels), on forced tokens."""
+    base = W.get("small_bf16")
+    w = W.scaled(base, "batches", n_layers=2, feat_layers=(0, 1), vocab=1024, n_seq=1, seq_len=400,
+                 anchors_per_seq=257, anchor_lo=100, anchor_hi=399, block=3)
+    inp = W.Inputs(w, W.random_weights(w.shape, 7, scale=0.05, norm_gain="random"),
+                   W.random_tokens(1024, (1, 400), 8), *W.random_anchors(1, 400, 257, 100, 399, 9),
+                   None, None)
+    eng = make_engine(inp)
+    prefill(eng, inp)
+    forced = torch.from_numpy(W.random_tokens(1024, (257, 3), 10)).cuda()
+    _, lp, ft = eng.rollout(inp.anchor_seq, inp.anchor_pos, 3, forced=forced)
+    for n in (1, 32, 33, 64, 65, 128, 129, 256):
+        _, lpn, ftn = eng.rollout(inp.anchor_seq[:n], inp.anchor_pos[:n], 3, forced=forced[:n])
+        # one bf16 rounding of an operand moves by at most 2^-8 of its value
+        for x, y in ((lpn, lp[:n]), (ftn, ft[:n])):
+            rel = float((x - y).norm() / y.norm())
+            assert rel <= 2 ** -8, (n, rel)
+        assert torch.equal(ftn[:, 0], ft[:n, 0])  # slot 0 is the prefill's row
+    eng.close()
+
+
 # ------------------------------------------------------------------ fp32 workload
 def _full_compare(inp, sel=None, block=None):
     w = inp.workload
