@@ -22,13 +22,13 @@ extern "C" {
  * multiples of 64 (ALR_E_UNSUPPORTED otherwise).  `tile` picks the bf16
  * kernel: 0 = the library's choice for this shape; W staged through LDS:
  * 1 = 256x128, 2 = 128x128, 3 = 64x128, 4 = 256x256 (8 waves), 5 = 256x256
- * (4 waves); 17 = ping-pong (the two waves of each SIMD alternate LDS and
- * MFMA phases) over register-staged BK = 64 tiles, one tile per workgroup
- * (K a multiple of 64); 18 = split-K over the ping-pong kernel (K slices
- * summed in slice order by a second kernel; 2 or 4 slices by the library's
- * rule, at least 2; K a multiple of 128); 19 = the ping-pong kernel of 17 run
+ * (4 waves); 17 = 256x256 with the operands copied straight into LDS and a
+ * hand-scheduled K loop, one tile per workgroup; 18 = split-K over that kernel
+ * (K slices of at least 192 summed in slice order by a second kernel; 2 or 4
+ * slices, the unsplit kernel when K allows none); 19 = the kernel of 17 run
  * persistently (one workgroup per CU looping over the tiles, the next tile's
- * first k-steps loaded during the current tile's last ones); 20 = split-K
+ * first K steps copied during the current tile's epilogue); 17 to 19 run as 3
+ * when K < 192; 20 = split-K
  * over the 64x128 kernel of 3 (2 or 4 slices, each a multiple of 64; the
  * unsplit kernel of 3 when K allows no split).  Other values:
  * ALR_E_INVALID_ARG.  Tiles 18 and 20 need a device scratch buffer of at

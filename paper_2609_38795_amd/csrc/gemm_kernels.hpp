@@ -1,11 +1,9 @@
 // GEMM kernels C[M,N] = A[M,K] * W[N,K]^T with fused epilogues (gfx950).
 //
-// bf16 path: 32x32x16 bf16 MFMA with fp32 accumulation.  Large GEMMs use the
-// 256x256 ping-pong kernel over register-staged BK = 64 tiles, run
-// persistently (gemm_bf16_pp64p_kernel; gemm_bf16_pp64_kernel is the same
-// schedule one tile per workgroup, used for split-K); GEMMs with fewer than
-// 256 such tiles use the LDS-staged gemm_bf16_kernel at 128x128 or 64x128, and
-// products of few rows gemm_bf16_ring_kernel.
+// bf16 path: MFMA with fp32 accumulation.  Large GEMMs use 256x256 tiles with a
+// hand-scheduled K loop (gemm_wide.hpp), products of few rows
+// gemm_bf16_ring_kernel, and what lies between the LDS-staged gemm_bf16_kernel at
+// 128x128.
 // fp32 path: FMA, 64x64x16 tile.  Both hand the epilogue *pairs* of outputs:
 // the value at column c and the one at column c+32, where c lies in the low
 // half of a 64-column group.
@@ -169,21 +167,21 @@ struct EpiQKV {
       *(f32x4*)p = x;
     }
   }
-  // NR (4 or 16) rows of a lane's 32-row block (row of index t: rb + 8 (t >> 2) +
+  // NR (4 or 16) rows of a lane (row of index t: rb + QS (t >> 2) +
   // (t & 3); rows >= M are skipped) of columns c and c+32.  Every load the
   // rows need (positions, then cos/sin, or the V^T columns) is issued before
   // any store, so the block costs two memory round trips rather than one per
   // row.  Four consecutive, 4-aligned columns of the transposed V cache go out
   // as one 8-byte store per column (bf16).
   static constexpr bool by_rows = true;
-  template <int NR>
+  template <int NR, int QS = 8>
   __device__ __forceinline__ void rows(int rb, int M, int c, const float* lo,
                                        const float* hi) const {
     const int half = hd >> 1;
     const int qd = H * hd, kd = G * hd;
     int r[NR];
 #pragma unroll
-    for (int t = 0; t < NR; ++t) r[t] = rb + 8 * (t >> 2) + (t & 3);
+    for (int t = 0; t < NR; ++t) r[t] = rb + QS * (t >> 2) + (t & 3);
     if (c < qd + kd) {
       OutT* base;
       long rs;
@@ -273,14 +271,19 @@ struct EpiQKV {
 };
 
 // Epilogues that read memory, or that write two columns per access, define
-// rows<NR>(): a lane's 16 rows of a 32-row block (or four of them) at once, all
-// loads before all stores (the compiler cannot prove that a later row's load
+// rows<NR, QS>(): NR rows of a lane at once (quads of rows QS apart: 8 in a 32x32
+// accumulator, 16 in a column of 16x16 ones), all loads before all stores (the compiler cannot prove that a later row's load
 // does not alias an earlier row's store, so element-wise calls would wait for
 // one load round trip per row).
 template <class Epi, class = void>
 struct has_rows : std::false_type {};
 template <class Epi>
 struct has_rows<Epi, decltype((void)Epi::by_rows)> : std::true_type {};
+
+template <class Epi, class = void>
+struct has_rows64 : std::false_type {};
+template <class Epi>
+struct has_rows64<Epi, decltype((void)Epi::by_rows64)> : std::true_type {};
 
 // Residual add into the fp32 stream, optionally capturing the new value as a
 // feature row: feat + (perm ? perm[row] : row) * feat_rs.
@@ -309,21 +312,21 @@ struct EpiResid {
   // permutation indices) two halves of 8 rows bound the registers the
   // epilogue needs inside a persistent kernel.
   static constexpr bool by_rows = true;
-  template <int NR>
+  template <int NR, int QS = 8>
   __device__ __forceinline__ void rows(int rb, int M, int c, const float* lo,
                                        const float* hi) const {
     if (!feat) {
       float a[NR], b[NR];
 #pragma unroll
       for (int t = 0; t < NR; ++t) {
-        const int rc = min(rb + 8 * (t >> 2) + (t & 3), M - 1);
+        const int rc = min(rb + QS * (t >> 2) + (t & 3), M - 1);
         const float* p = h + (long)rc * ld + c;
         a[t] = p[0];
         b[t] = p[32];
       }
 #pragma unroll
       for (int t = 0; t < NR; ++t) {
-        const int r = rb + 8 * (t >> 2) + (t & 3);
+        const int r = rb + QS * (t >> 2) + (t & 3);
         if (r < M) {
           float* p = h + (long)r * ld + c;
           p[0] = a[t] + lo[t];
@@ -340,7 +343,7 @@ struct EpiResid {
 #pragma unroll
       for (int u = 0; u < HR; ++u) {
         const int t = HR * half + u;
-        const int r = rb + 8 * (t >> 2) + (t & 3), rc = min(r, M - 1);
+        const int r = rb + QS * (t >> 2) + (t & 3), rc = min(r, M - 1);
         const float* p = h + (long)rc * ld + c;
         a[u] = p[0];
         b[u] = p[32];
@@ -349,7 +352,7 @@ struct EpiResid {
 #pragma unroll
       for (int u = 0; u < HR; ++u) {
         const int t = HR * half + u;
-        const int r = rb + 8 * (t >> 2) + (t & 3);
+        const int r = rb + QS * (t >> 2) + (t & 3);
         if (r < M) {
           a[u] += lo[t];
           b[u] += hi[t];
@@ -385,7 +388,7 @@ struct EpiSwiGLU {
   // lane-pair exchange (pair_rows); the pair's first output column is even
   // because d_ffn is a multiple of 64.
   static constexpr bool by_rows = true;
-  template <int NR>
+  template <int NR, int QS = 8>
   __device__ __forceinline__ void rows(int rb, int M, int c, const float* lo,
                                        const float* hi) const {
     const int odd = c & 1;
@@ -396,7 +399,7 @@ struct EpiSwiGLU {
 #pragma unroll
     for (int t = 0; t < NR; t += 2) {
       const f32x2 x = pair_rows(odd, y[t], y[t + 1]);
-      const int r = rb + 8 * (t >> 2) + (t & 3) + odd;
+      const int r = rb + QS * (t >> 2) + (t & 3) + odd;
       if (r < M) {
         if constexpr (std::is_same<OutT, bf16>::value)
           *(uint32_t*)(out + (long)r * ld + col) = pack2bf(x[0], x[1]);
@@ -450,18 +453,18 @@ struct EpiLogits {
     }
   }
   static constexpr bool by_rows = true;
-  template <int NR>
+  template <int NR, int QS = 8>
   __device__ __forceinline__ void rows(int rb, int M, int c, const float* lo,
                                        const float* hi) const {
     int rr[NR];
 #pragma unroll
     for (int t = 0; t < NR; ++t) {
-      const int r = rb + 8 * (t >> 2) + (t & 3);
+      const int r = rb + QS * (t >> 2) + (t & 3);
       rr[t] = perm ? perm[min(r, M - 1)] : r;
     }
 #pragma unroll
     for (int t = 0; t < NR; ++t)
-      if (rb + 8 * (t >> 2) + (t & 3) < M) {
+      if (rb + QS * (t >> 2) + (t & 3) < M) {
         float* p = out + (long)rr[t] * rs + c;
         p[0] = lo[t];
         p[32] = hi[t];
@@ -475,8 +478,40 @@ struct EpiLogits {
         const LogitPart q = half_wave_part(lo[t], hi[t]);
         if (lr == t) mine = q;
       }
-      const int r = rb + 8 * (lr >> 2) + (lr & 3);
+      const int r = rb + QS * (lr >> 2) + (lr & 3);
       if (lr < NR && r < M) part[(long)r * part_ld + (c >> 6)] = mine;
+    }
+  }
+  // 16 rows of the columns c, c + 16, c + 32, c + 48 of a 64-column group, whose
+  // other columns the 16-lane row holds.
+  static constexpr bool by_rows64 = true;
+  __device__ __forceinline__ void rows64(int rb, int M, int c, const float (&v)[4][16]) const {
+    int rr[16];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+      const int r = rb + 16 * (t >> 2) + (t & 3);
+      rr[t] = perm ? perm[min(r, M - 1)] : r;
+    }
+#pragma unroll
+    for (int t = 0; t < 16; ++t)
+      if (rb + 16 * (t >> 2) + (t & 3) < M) {
+        float* p = out + (long)rr[t] * rs + c;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) p[16 * j] = v[j][t];
+      }
+    if (part) {
+      const int lc = threadIdx.x & 15;
+      const float l2e = 1.44269504088896341f;
+      LogitPart mine = {0.f, 0.f};
+#pragma unroll
+      for (int t = 0; t < 16; ++t) {
+        const float m = group_max<16>(fmaxf(fmaxf(v[0][t], v[1][t]), fmaxf(v[2][t], v[3][t])));
+        const float s = group_sum<16>((fast_exp2((v[0][t] - m) * l2e) + fast_exp2((v[1][t] - m) * l2e)) +
+                                      (fast_exp2((v[2][t] - m) * l2e) + fast_exp2((v[3][t] - m) * l2e)));
+        if (lc == t) mine = {m, s};
+      }
+      const int r = rb + 16 * (lc >> 2) + (lc & 3);  // lane t of the 16 stores row t
+      if (r < M) part[(long)r * part_ld + (c >> 6)] = mine;
     }
   }
 };
@@ -836,248 +871,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, OCC) void gemm_bf16_kernel(
   }
 
   gemm_store_tile<MI, NI>(epi, acc, m0 + wm * WTM, n0 + wn * WTN, M, N);
-}
-
-// ------------------------------------------------------------------ bf16 MFMA GEMM, ping-pong, BK = 64
-//
-// 256x256 tile, 8 waves, two LDS stages of BK = 64 (rows of 128 bytes, so every
-// global request is a whole cache line).  Groups as in gemm_bf16_pp_kernel
-// (waves w and w+4 share a SIMD; group g owns rows [128 g, 128 g + 128)).  A
-// step is consumed in two half-steps u = 2s + h (k-slices 2h, 2h+1), each a
-// memory phase then a compute phase per group, group 1 one phase behind.
-//
-// Memory phase of half-step (s, h): read this half-step's fragments from
-// stage s % 2; write the registers holding half h of step s+1 (h = 0: A rows,
-// h = 1: W rows) into stage (s+1) % 2; load half h of step s+2 into the same
-// registers.  Loads therefore have one step of latency cover, and a stage is
-// rewritten only after both groups finished reading it (the barrier after the
-// last memory phase of step s-1).  Each memory phase ends with its LDS work
-// complete, so the barrier publishes the writes.
-// With splits > 1 the grid holds `splits` workgroups per tile: workgroup b
-// computes K slice b % splits (K is then the slice length; A and W advance by
-// slice * K columns) of tile b / splits, for an epilogue with set_split.
-template <int TAG, class Epi>
-__global__ __launch_bounds__(512, 1) void gemm_bf16_pp64_kernel(
-    const bf16* __restrict__ A, int lda, const bf16* __restrict__ W, int ldw, int M, int N, int K,
-    int tiles_m, int tiles_n, Epi epi, int splits = 1) {
-  constexpr int BM = 256, BN = 256, BK = 64;
-  constexpr int WTM = 128, WTN = 64, MI = 4, NI = 2;
-  constexpr int STAGE = (BM + BN) * BK;  // bf16 elements
-  __shared__ __attribute__((aligned(1024))) bf16 smem[2 * STAGE];
-
-  int bid = blockIdx.x;
-  if constexpr (has_set_split<Epi>::value) {
-    if (splits > 1) {
-      const int sl = bid % splits;
-      bid /= splits;
-      A += (long)sl * K;
-      W += (long)sl * K;
-      epi.set_split(sl);
-    }
-  }
-  int tm, tn;
-  gemm_tile_coords(bid, tiles_m, tiles_n, tm, tn);
-  const int m0 = tm * BM, n0 = tn * BN;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int grp = wave >> 2;
-  const int wm = grp, wn = wave & 3;
-
-  // half 0 = the A tile (256 rows x 8 chunks), half 1 = the W tile; thread t
-  // moves chunks t + 512 i, i = 0..3, of each half.
-  uint32_t goff[2][4];
-  int loff[2][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int ch = tid + 512 * i, r = ch >> 3, c = ch & 7;
-    goff[0][i] = (uint32_t)(((long)min(m0 + r, M - 1) * lda + c * 8) * 2);
-    goff[1][i] = (uint32_t)(((long)min(n0 + r, N - 1) * ldw + c * 8) * 2);
-    loff[0][i] = swz<BK>(r, c);
-    loff[1][i] = BM * BK + swz<BK>(r, c);
-  }
-  const int nk = K / BK;
-  const char* gbase[2] = {(const char*)A, (const char*)W};
-  auto gload = [&](GemmRegs<4>& rg, int h, int step) {
-    const char* b = gbase[h] + (long)min(step, nk - 1) * BK * 2;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) rg.v[i] = *(const u32x4*)(b + goff[h][i]);
-  };
-  auto lstore = [&](const GemmRegs<4>& rg, int h, bf16* stage) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) *(u32x4*)(stage + loff[h][i]) = rg.v[i];
-  };
-
-  GemmRegs<4> rg[2];
-  gload(rg[0], 0, 0);
-  gload(rg[1], 1, 0);
-  lstore(rg[0], 0, smem);
-  lstore(rg[1], 1, smem);
-  gload(rg[0], 0, 1);
-  gload(rg[1], 1, 1);
-  __syncthreads();
-  if (grp == 1) __builtin_amdgcn_s_barrier();  // group 1 runs one phase behind
-
-  f32x16 acc[MI][NI];
-#pragma unroll
-  for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
-
-  GemmFrag<MI, NI> f0, f1;
-  for (int kt = 0; kt < nk; ++kt) {
-    const bf16* cur = smem + (kt & 1) * STAGE;
-    bf16* nxt = smem + ((kt + 1) & 1) * STAGE;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      // memory phase
-      __builtin_amdgcn_sched_barrier(0);
-      gemm_frag_load<BK, MI, NI, WTM, WTN>(f0, cur, cur + BM * BK, wm, wn, 2 * h);
-      gemm_frag_load<BK, MI, NI, WTM, WTN>(f1, cur, cur + BM * BK, wm, wn, 2 * h + 1);
-      lstore(rg[h], h, nxt);
-      gload(rg[h], h, kt + 2);
-      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): fragments read, stage writes done
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-      // compute phase
-      __builtin_amdgcn_s_setprio(1);
-      gemm_frag_mma<MI, NI>(f0, acc);
-      gemm_frag_mma<MI, NI>(f1, acc);
-      __builtin_amdgcn_s_setprio(0);
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_barrier();
-    }
-  }
-  if (grp == 0) __builtin_amdgcn_s_barrier();
-
-  gemm_store_tile<MI, NI>(epi, acc, m0 + wm * WTM, n0 + wn * WTN, M, N);
-}
-
-// ------------------------------------------------------------------ bf16 MFMA GEMM, ping-pong, persistent
-//
-// gemm_bf16_pp64_kernel's schedule run by one workgroup per CU over tiles
-// blockIdx.x, blockIdx.x + gridDim.x, ...  The k-steps of consecutive tiles
-// form one stream: in the last two k-steps of a tile the global loads already
-// fetch the next tile's first two steps, and the LDS stage parity runs on
-// across tiles.  A group's epilogue sits between its last compute phase of a
-// tile and its first memory phase of the next, i.e. while the other group
-// computes, so the pipeline is neither drained nor refilled between tiles.
-template <int TAG, class Epi>
-__global__ __launch_bounds__(512, 1) void gemm_bf16_pp64p_kernel(
-    const bf16* __restrict__ A, int lda, const bf16* __restrict__ W, int ldw, int M, int N, int K,
-    int tiles_m, int tiles_n, Epi epi) {
-  constexpr int BM = 256, BN = 256, BK = 64;
-  constexpr int WTM = 128, WTN = 64, MI = 4, NI = 2;
-  constexpr int STAGE = (BM + BN) * BK;  // bf16 elements
-  __shared__ __attribute__((aligned(1024))) bf16 smem[2 * STAGE];
-
-  const int ntiles = tiles_m * tiles_n;
-  int tile = blockIdx.x;
-  if (tile >= ntiles) return;  // uniform over the workgroup
-  const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int grp = wave >> 2;
-  const int wm = grp, wn = wave & 3;
-  const int nk = K / BK;
-
-  // thread t moves chunks t + 512 i (row ch >> 3, 16-byte chunk ch & 7) of
-  // the A tile (half 0) and of the W tile (half 1)
-  int loff[2][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int ch = tid + 512 * i, r = ch >> 3, c = ch & 7;
-    loff[0][i] = swz<BK>(r, c);
-    loff[1][i] = BM * BK + swz<BK>(r, c);
-  }
-  auto offsets = [&](int t, uint32_t (&go)[2][4]) {
-    int tm, tn;
-    gemm_tile_coords(t, tiles_m, tiles_n, tm, tn);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int ch = tid + 512 * i, r = ch >> 3, c = ch & 7;
-      go[0][i] = (uint32_t)(((long)min(tm * BM + r, M - 1) * lda + c * 8) * 2);
-      go[1][i] = (uint32_t)(((long)min(tn * BN + r, N - 1) * ldw + c * 8) * 2);
-    }
-  };
-  uint32_t gcur[2][4], gnxt[2][4];
-  int next = tile + gridDim.x;
-  offsets(tile, gcur);
-  offsets(next < ntiles ? next : tile, gnxt);
-  const char* gbase[2] = {(const char*)A, (const char*)W};
-  // step s of the stream relative to the current tile: s < nk is the current
-  // tile, s >= nk the next one (or the current tile's last step when there is
-  // none; those loads are never used)
-  auto gload = [&](GemmRegs<4>& rg, int h, int s) {
-    const bool nx = s >= nk;
-    const int st = nx ? (next < ntiles ? s - nk : nk - 1) : s;
-    const char* b = gbase[h] + (long)st * BK * 2;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) rg.v[i] = *(const u32x4*)(b + (nx ? gnxt[h][i] : gcur[h][i]));
-  };
-  auto lstore = [&](const GemmRegs<4>& rg, int h, bf16* stage) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) *(u32x4*)(stage + loff[h][i]) = rg.v[i];
-  };
-
-  GemmRegs<4> rg[2];
-  gload(rg[0], 0, 0);
-  gload(rg[1], 1, 0);
-  lstore(rg[0], 0, smem);
-  lstore(rg[1], 1, smem);
-  gload(rg[0], 0, 1);
-  gload(rg[1], 1, 1);
-  __syncthreads();
-  if (grp == 1) __builtin_amdgcn_s_barrier();  // group 1 runs one phase behind
-
-  f32x16 acc[MI][NI];
-  GemmFrag<MI, NI> f0, f1;
-  int gs = 0;  // k-steps done by this workgroup over all its tiles
-  while (true) {
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
-    for (int kt = 0; kt < nk; ++kt, ++gs) {
-      const bf16* cur = smem + (gs & 1) * STAGE;
-      bf16* nxt = smem + ((gs + 1) & 1) * STAGE;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        // memory phase
-        __builtin_amdgcn_sched_barrier(0);
-        gemm_frag_load<BK, MI, NI, WTM, WTN>(f0, cur, cur + BM * BK, wm, wn, 2 * h);
-        gemm_frag_load<BK, MI, NI, WTM, WTN>(f1, cur, cur + BM * BK, wm, wn, 2 * h + 1);
-        lstore(rg[h], h, nxt);
-        gload(rg[h], h, kt + 2);
-        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): fragments read, stage writes done
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        // compute phase
-        __builtin_amdgcn_s_setprio(1);
-        gemm_frag_mma<MI, NI>(f0, acc);
-        gemm_frag_mma<MI, NI>(f1, acc);
-        __builtin_amdgcn_s_setprio(0);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_barrier();
-      }
-    }
-    int tm, tn;
-    gemm_tile_coords(tile, tiles_m, tiles_n, tm, tn);
-    gemm_store_tile<MI, NI>(epi, acc, tm * BM + wm * WTM, tn * BN + wn * WTN, M, N);
-    if (next >= ntiles) break;
-    tile = next;
-    next = tile + gridDim.x;
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) gcur[hh][i] = gnxt[hh][i];
-    if (next < ntiles) offsets(next, gnxt);
-  }
-  if (grp == 0) __builtin_amdgcn_s_barrier();
 }
 
 // ------------------------------------------------------------------ bf16 MFMA GEMM, few rows

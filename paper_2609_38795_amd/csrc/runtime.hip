@@ -31,6 +31,7 @@
 #include "../../include/alr_debug.h"
 #include "attn_kernels.hpp"
 #include "gemm_kernels.hpp"
+#include "gemm_wide.hpp"
 #include "misc_kernels.hpp"
 
 using namespace alr;
@@ -156,8 +157,8 @@ alr_status check_operand_sizes(const alr_config& c, const alr_limits& lim, char*
   return ALR_OK;
 }
 
-// Products of at most this many rows run on the ring kernels (pick_ring).
-constexpr int RING_MAX_ROWS = 256;
+// Up to this many rows a product may be cut into 8 K slices (pick_gemm).
+constexpr int FEW_ROWS = 256;
 
 int anchor_group(const alr_config& c) { return std::max(1, 128 / (c.n_heads / c.n_kv_heads)); }
 
@@ -258,7 +259,7 @@ size_t compute_layout(const alr_config& c, const alr_limits& lim, Layout& L) {
   L.part_ml = take(L.max_dwork * 128 * 2 * 4);
   // split-K partial sums of the rollout GEMMs: up to 4 slices of [anchors, N] fp32,
   // and up to 8 where there are few rows
-  L.splitk_bytes = std::max(4 * NA, 8 * std::min<size_t>(NA, RING_MAX_ROWS)) *
+  L.splitk_bytes = std::max(4 * NA, 8 * std::min<size_t>(NA, FEW_ROWS)) *
                    std::max(qd + 2 * kvd, d) * 4;
   L.splitk = take(L.splitk_bytes);
   L.total = off;
@@ -488,41 +489,58 @@ bool launch_splitk_resid_norm(alr_ctx* ctx, int S, int M, int N, const EpiResid&
   return true;
 }
 
-// Kernel and K slices of a product of few rows (M <= RING_MAX_ROWS).  Such a
-// product reads its weights once whatever the choice; beyond that a kernel
-// takes about `step_us` per K step of a workgroup (barrier, operand reads and
-// the copies the step waits for; measured over K = 1024 .. 18944), workgroups
-// beyond one per CU queue behind the first, and slices cost the fp32 partials
-// they write and re-read plus a second launch unless that is the reduce which
-// carries the following RMSNorm.  The choice minimises the sum:
-//   rows   tile      us/step   e.g. N = 6144, K = 4096 (unsplit 64x128 tiles: 33)
-//   <= 32   32 x 64    0.26    2 slices 11.8 us
-//   <= 64   64 x 64    0.34    4 slices 13.4 us
-//   else   128 x 64    0.47    2 slices 18.4 us (M = 128)
-//          128 x 128   0.57    4 slices 15.2 us (M = 128)
-struct RingPlan {
+// Kernel and K slices of a bf16 product, by the estimated time of each choice.
+// A round of workgroups, one per CU, takes steps x (time of a K step of 64) plus
+// what a tile costs besides its K loop; slices add the fp32 partials they write
+// and re-read (4.2 TB/s) and a second launch, unless that is the reduce which
+// carries the following RMSNorm.  The constants are fits over M = 7 .. 8192, N =
+// 1024 .. 37888, K = 1024 .. 18944 (weights rotated through more than the last-level
+// cache).  A step of the 256x256 kernel takes longer the more CUs run it, as the
+// clock falls: 1.03 us on half of them, 1.35 us on all.  Where the lines lie:
+//   M <= 64 streams weights, so the 32- and 64-row tiles win; at M = 128 the 128-row
+//   ring tiles do (N = 28672, K = 4096: 52 us against 69 for 64x128 LDS-staged
+//   tiles and 85 for 256x256); from M = 256 on the 256x256 tiles, sliced so that
+//   they fill the CUs (M = 1024, N = 6144, K = 4096: 2 slices 48 us, 128x128 63;
+//   M = 2048: unsliced 83, 128x128 117).  128x128 LDS-staged tiles remain where
+//   256x256 ones would leave CUs idle and K is too short to slice (M = 8192,
+//   N = 1024, K = 1024: 23.6 against 25.7 us).
+enum class Gemm { ring32, ring64, ring128x64, ring128, lds128, wide };
+struct GemmPlan {
+  Gemm kernel;
   int bm, bn, splits;
 };
-RingPlan pick_ring(int M, int N, int K, int n_cu, size_t split_bytes, bool norm_follows) {
+//   epi_us: what the unsliced 256x256 kernel's epilogue takes beyond plain stores.
+GemmPlan pick_gemm(int M, int N, int K, int n_cu, size_t split_bytes, bool norm_follows,
+                   float epi_us) {
   struct Kern {
+    Gemm k;
     int bm, bn;
-    float step_us;
+    float step_us, tile_us;
   };
-  static const Kern kerns[] = {{32, 64, 0.26f}, {64, 64, 0.34f}, {128, 64, 0.47f}, {128, 128, 0.57f}};
-  RingPlan best{0, 0, 0};
+  static const Kern kerns[] = {
+      {Gemm::ring32, 32, 64, 0.26f, 2.f},      {Gemm::ring64, 64, 64, 0.34f, 2.f},
+      {Gemm::ring128x64, 128, 64, 0.47f, 2.f}, {Gemm::ring128, 128, 128, 0.57f, 3.f},
+      {Gemm::lds128, 128, 128, 0.58f, 2.3f},   {Gemm::wide, 256, 256, 0.f, 10.f}};
+  GemmPlan best{Gemm::ring32, 0, 0, 0};
   float best_us = 0.f;
   for (const Kern& k : kerns) {
-    if (M <= 32 ? k.bm != 32 : (M <= 64 ? k.bm != 64 : k.bm != 128)) continue;
-    const int t = ((M + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn);
+    // the smallest row tile that holds M, or tiles of 128 rows and more
+    if (k.bm == 32 ? M > 32 : (k.bm == 64 ? M <= 32 || M > 64 : M <= 64)) continue;
+    if (k.k == Gemm::lds128 && M <= FEW_ROWS) continue;  // the ring kernel of that tile is faster
+    const long t = (long)((M + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn);
     for (int S = 1; S <= 8; S *= 2) {
-      if (S > 1 && ((long)t * S > n_cu || K % (64 * S) != 0 || K / S < 256 ||
-                    (size_t)S * M * N * 4 > split_bytes || (S == 8 && N > 4096)))
+      if (k.k == Gemm::wide && K / S < 192) continue;
+      if (S > 1 && (k.k == Gemm::lds128 || t * S > n_cu || K % (64 * S) != 0 || K / S < 256 ||
+                    (size_t)S * M * N * 4 > split_bytes || (S == 8 && (N > 4096 || M > FEW_ROWS))))
         continue;
-      const int rounds = (t * S + n_cu - 1) / n_cu;
-      float us = (float)(K / 64 / S) * k.step_us * rounds;
-      if (S > 1) us += 2e-6f * S * M * N + (norm_follows ? 0.f : 5.f);
+      const long rounds = (t * S + n_cu - 1) / n_cu;
+      const float busy = std::min(1.f, (float)(t * S) / n_cu);
+      const float step = k.k == Gemm::wide ? 0.7f + 0.65f * busy : k.step_us;
+      float us = (float)rounds * ((float)(K / 64 / S) * step + k.tile_us +
+                                  (k.k == Gemm::wide && S == 1 ? epi_us : 0.f));
+      if (S > 1) us += (float)S * M * N * (4.f / 4.2e6f) + (norm_follows ? 0.f : 3.f);
       if (best.splits == 0 || us < best_us) {
-        best = RingPlan{k.bm, k.bn, S};
+        best = GemmPlan{k.k, k.bm, k.bn, S};
         best_us = us;
       }
     }
@@ -531,22 +549,34 @@ RingPlan pick_ring(int M, int N, int K, int n_cu, size_t split_bytes, bool norm_
 }
 
 template <int TAG, class Epi>
-void launch_ring(const RingPlan& p, const bf16* A, int lda, const bf16* W, int ldw, int M, int N,
-                 int K, const Epi& epi, hipStream_t st) {
+void launch_plan(const GemmPlan& p, int n_cu, const bf16* A, int lda, const bf16* W, int ldw,
+                 int M, int N, int K, const Epi& epi, hipStream_t st) {
   const int tm = (M + p.bm - 1) / p.bm, tn = (N + p.bn - 1) / p.bn;
   const unsigned grid = (unsigned)((tn * p.splits + 7) / 8 * 8 * tm);
   const int Ks = K / p.splits;
 #define ALR_RING(BM_, BN_, WGM_, WGN_, WGK_, ST_)                                  \
   gemm_bf16_ring_kernel<TAG, BM_, BN_, WGM_, WGN_, WGK_, ST_, Epi>                 \
       <<<grid, 64 * WGM_ * WGN_ * WGK_, 0, st>>>(A, lda, W, ldw, M, N, Ks, tm, tn, epi, p.splits)
-  if (p.bm == 32)
-    ALR_RING(32, 64, 1, 1, 4, 5);
-  else if (p.bm == 64)
-    ALR_RING(64, 64, 2, 1, 2, 4);
-  else if (p.bn == 64)
-    ALR_RING(128, 64, 4, 1, 1, 3);
-  else
-    ALR_RING(128, 128, 4, 2, 1, 4);
+  switch (p.kernel) {
+    case Gemm::ring32: ALR_RING(32, 64, 1, 1, 4, 5); break;
+    case Gemm::ring64: ALR_RING(64, 64, 2, 1, 2, 4); break;
+    case Gemm::ring128x64: ALR_RING(128, 64, 4, 1, 1, 3); break;
+    case Gemm::ring128: ALR_RING(128, 128, 4, 2, 1, 4); break;
+    case Gemm::lds128:
+      if constexpr (!has_set_split<Epi>::value) {  // never sliced
+        if (K % 128 == 0)
+          gemm_bf16_kernel<TAG, 128, 128, 2, 2, 64, 2, Epi>
+              <<<tm * tn, 256, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
+        else
+          gemm_bf16_kernel<TAG, 128, 128, 2, 2, 32, 2, Epi>
+              <<<tm * tn, 256, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
+      }
+      break;
+    case Gemm::wide:
+      gemm_bf16_wide_kernel<TAG, Epi><<<std::min(tm * tn * p.splits, n_cu), 256, 0, st>>>(
+          A, lda, W, ldw, M, N, Ks, tm, tn, epi, p.splits);
+      break;
+  }
 #undef ALR_RING
 }
 
@@ -560,35 +590,18 @@ void launch_gemm(alr_ctx* ctx, const T* A, int lda, const T* W, int ldw, int M, 
   if (M <= 0) return;
   ProfScope ps(ctx, TAG, st);
   if constexpr (std::is_same<T, bf16>::value) {
-    // W row-major.  256x256 ping-pong (BK = 64), persistent over the tiles, for
-    // the prefill and wide decode GEMMs, 128x128 (then 64x128) LDS-staged tiles
-    // where 256x256 would leave CUs idle.  force_tile (debug hook only) picks any variant.
-    auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-    int cfg = force_tile;
-    // Split-K over the 256x256 ping-pong kernel when its tiles leave CUs idle:
-    // the largest slice count in {2, 4} that keeps one workgroup per CU, K
-    // slices of >= 512 and a multiple of 64, and the partial sums in the buffer.
-    // Where 128x128 tiles alone give every CU the same number of tiles and
-    // K <= 4096, writing and re-reading the fp32 partial sums costs more than
-    // the ping-pong kernel gains (M = 1024, N = 4096: 46 vs 55 us), so those
-    // GEMMs take the 128x128 kernel with the epilogue fused (also where the
-    // split-K reduce would carry the following RMSNorm: 29.5 vs 26.3 + 2.9 ms
-    // per step for the rollout O projection).  With uneven rounds (N = 6144:
-    // 384 tiles on 256 CUs) split-K stays ahead.
-    const bool fill128 = K <= 4096 && tiles(128, 128) % ctx->n_cu == 0;
     // the output head's per-group partials are formed in the epilogue of each
     // tile; a split-K reduce hands it columns in another arrangement
     bool epi_whole_k = false;
     if constexpr (std::is_same<Epi, EpiLogits>::value) epi_whole_k = epi.part != nullptr;
-    if (cfg == 0 && M <= RING_MAX_ROWS) {
-      const bool may_split = ctx->splitk_buf != nullptr && !epi_whole_k;
-      const RingPlan p = pick_ring(M, N, K, ctx->n_cu, may_split ? ctx->splitk_bytes : 0,
-                                   norm_out != nullptr);
+    const bool may_split = ctx->splitk_buf != nullptr && !epi_whole_k;
+    auto run = [&](const GemmPlan& p) {
       if (p.splits == 1) {
-        launch_ring<TAG>(p, A, lda, W, ldw, M, N, K, epi, st);
+        launch_plan<TAG>(p, ctx->n_cu, A, lda, W, ldw, M, N, K, epi, st);
         return;
       }
-      launch_ring<TAG>(p, A, lda, W, ldw, M, N, K, EpiPartial{ctx->splitk_buf, (long)M * N, N}, st);
+      launch_plan<TAG>(p, ctx->n_cu, A, lda, W, ldw, M, N, K,
+                       EpiPartial{ctx->splitk_buf, (long)M * N, N}, st);
       if constexpr (std::is_same<Epi, EpiResid>::value) {
         if (norm_out && normed &&
             launch_splitk_resid_norm<T>(ctx, p.splits, M, N, epi, norm_g, norm_out, st)) {
@@ -597,96 +610,61 @@ void launch_gemm(alr_ctx* ctx, const T* A, int lda, const T* W, int ldw, int M, 
         }
       }
       launch_splitk_reduce(ctx->splitk_buf, (long)M * N, p.splits, M, N, epi, st);
+    };
+    if (force_tile == 0) {
+      // all CUs reach their epilogues together, with nothing to hide loads behind
+      const float epi_us = has_rows<Epi>::value && !std::is_same<Epi, EpiSwiGLU<bf16>>::value ? 14.f : 0.f;
+      run(pick_gemm(M, N, K, ctx->n_cu, may_split ? ctx->splitk_bytes : 0, norm_out != nullptr, epi_us));
       return;
     }
-    // Few rows (the rollout of a small batch): when even split-K leaves more
-    // than half the CUs without a 256x256 tile, 64x128 tiles split over K
-    // (slices of >= 256 and a multiple of 64) spread the work over more CUs.
-    if ((cfg == 20 || (cfg == 0 && !fill128)) && ctx->splitk_buf != nullptr && !epi_whole_k) {
-      const int t256 = tiles(256, 256), t64 = tiles(64, 128);
-      int S256 = 1, S = 1;
-      for (int cand : {2, 4}) {
-        const bool fits = (size_t)cand * M * N * 4 <= ctx->splitk_bytes;
-        if ((long)t256 * cand <= ctx->n_cu && K % (64 * cand) == 0 && K / cand >= 512 && fits)
-          S256 = cand;
-        if ((long)t64 * cand <= ctx->n_cu && K % (64 * cand) == 0 &&
-            (K / cand >= 256 || cfg == 20) && fits)
-          S = cand;
-      }
-      if (S > 1 && (cfg == 20 || ((long)t256 * S256 < ctx->n_cu / 2 && t64 * S >= 2 * t256 * S256))) {
-        const int tm = (M + 63) / 64, tn = (N + 127) / 128;
-        EpiPartial ep{ctx->splitk_buf, (long)M * N, N};
-        if ((K / S) % 128 == 0)
-          gemm_bf16_kernel<TAG, 64, 128, 2, 2, 64, 2, EpiPartial>
-              <<<t64 * S, 256, 0, st>>>(A, lda, W, ldw, M, N, K / S, tm, tn, ep, S);
-        else
-          gemm_bf16_kernel<TAG, 64, 128, 2, 2, 32, 4, EpiPartial>
-              <<<t64 * S, 256, 0, st>>>(A, lda, W, ldw, M, N, K / S, tm, tn, ep, S);
-        if constexpr (std::is_same<Epi, EpiResid>::value) {
-          if (norm_out && normed && launch_splitk_resid_norm<T>(ctx, S, M, N, epi, norm_g, norm_out, st)) {
-            *normed = true;
-            return;
-          }
+    if constexpr (TAG == 0) {  // the debug hook's variants
+      int cfg = force_tile;
+      if (cfg == 18 || cfg == 20) {  // sliced: the most slices that keep one workgroup per CU
+        const int bm = cfg == 18 ? 256 : 64, bn = cfg == 18 ? 256 : 128;
+        const int tm = (M + bm - 1) / bm, tn = (N + bn - 1) / bn;
+        int S = 1;
+        for (int cand : {2, 4})
+          if ((cand == 2 || (long)tm * tn * cand <= ctx->n_cu) && K % (64 * cand) == 0 &&
+              (cfg == 20 || K / cand >= 192) && (size_t)cand * M * N * 4 <= ctx->splitk_bytes)
+            S = cand;
+        if (S > 1 && cfg == 18) {
+          run(GemmPlan{Gemm::wide, bm, bn, S});
+          return;
         }
-        launch_splitk_reduce(ctx->splitk_buf, (long)M * N, S, M, N, epi, st);
-        return;
-      }
-      if (cfg == 20) cfg = 3;
-    }
-    if ((cfg == 18 || (cfg == 0 && !fill128)) && ctx->splitk_buf != nullptr && !epi_whole_k) {
-      const int t256 = tiles(256, 256);
-      int S = 1;
-      for (int cand : {2, 4})
-        if ((long)t256 * cand <= ctx->n_cu && K % (64 * cand) == 0 && K / cand >= 512 &&
-            (size_t)cand * M * N * 4 <= ctx->splitk_bytes)
-          S = cand;
-      if (cfg == 18 && S == 1 && K % 128 == 0 && (size_t)2 * M * N * 4 <= ctx->splitk_bytes) S = 2;
-      if (S > 1 && (cfg == 18 || t256 < ctx->n_cu)) {
-        const int tm = (M + 255) / 256, tn = (N + 255) / 256;
-        EpiPartial ep{ctx->splitk_buf, (long)M * N, N};
-        gemm_bf16_pp64_kernel<TAG, EpiPartial>
-            <<<t256 * S, 512, 0, st>>>(A, lda, W, ldw, M, N, K / S, tm, tn, ep, S);
-        if constexpr (std::is_same<Epi, EpiResid>::value) {
-          if (norm_out && normed && launch_splitk_resid_norm<T>(ctx, S, M, N, epi, norm_g, norm_out, st)) {
-            *normed = true;
-            return;
-          }
+        if (S > 1) {
+          const EpiPartial ep{ctx->splitk_buf, (long)M * N, N};
+          if ((K / S) % 128 == 0)
+            gemm_bf16_kernel<TAG, 64, 128, 2, 2, 64, 2, EpiPartial>
+                <<<tm * tn * S, 256, 0, st>>>(A, lda, W, ldw, M, N, K / S, tm, tn, ep, S);
+          else
+            gemm_bf16_kernel<TAG, 64, 128, 2, 2, 32, 4, EpiPartial>
+                <<<tm * tn * S, 256, 0, st>>>(A, lda, W, ldw, M, N, K / S, tm, tn, ep, S);
+          launch_splitk_reduce(ctx->splitk_buf, (long)M * N, S, M, N, epi, st);
+          return;
         }
-        launch_splitk_reduce(ctx->splitk_buf, (long)M * N, S, M, N, epi, st);
-        return;
+        cfg = cfg == 18 ? 19 : 3;
       }
-      if (cfg == 18) cfg = 0;
-    }
-    if (cfg == 0)
-      cfg = tiles(256, 256) >= 256 ? 19 : (tiles(128, 128) >= 256 ? 2 : 3);  // K is a multiple of 64
-    const bool k64 = (K % 128) == 0;
-    const int bm = (cfg == 1 || cfg == 4 || cfg == 5 || cfg >= 17) ? 256 : (cfg == 3 ? 64 : 128);
-    const int bn = (cfg == 4 || cfg == 5 || cfg >= 17) ? 256 : 128;
-    const int tm = (M + bm - 1) / bm, tn = (N + bn - 1) / bn;
-    const int nb = tm * tn;
+      if (cfg >= 17 && K < 192) cfg = 3;  // the 256x256 kernel needs three K steps
+      const int bm = (cfg == 1 || cfg == 4 || cfg == 5 || cfg >= 17) ? 256 : (cfg == 3 ? 64 : 128);
+      const int bn = (cfg == 4 || cfg == 5 || cfg >= 17) ? 256 : 128;
+      const int tm = (M + bm - 1) / bm, tn = (N + bn - 1) / bn, nb = tm * tn;
+      const bool k64 = (K % 128) == 0;
 #define ALR_GEMM(BM_, BN_, WGM_, WGN_, BK_, OCC_)                                      \
   gemm_bf16_kernel<TAG, BM_, BN_, WGM_, WGN_, BK_, OCC_, Epi>                          \
       <<<nb, 64 * WGM_ * WGN_, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi)
-    if constexpr (TAG == 0) {  // the debug hook's variants
       switch (cfg) {
         case 17:
-          gemm_bf16_pp64_kernel<TAG, Epi><<<nb, 512, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
-          return;
-        case 5: if (k64) ALR_GEMM(256, 256, 2, 2, 64, 1); else ALR_GEMM(256, 256, 2, 2, 32, 1); return;
-        case 4: if (k64) ALR_GEMM(256, 256, 2, 4, 64, 1); else ALR_GEMM(256, 256, 2, 4, 32, 1); return;
-        case 1: if (k64) ALR_GEMM(256, 128, 2, 2, 64, 1); else ALR_GEMM(256, 128, 2, 2, 32, 1); return;
-        default: break;
+          gemm_bf16_wide_kernel<TAG, Epi><<<nb, 256, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi, 1);
+          break;
+        case 19: run(GemmPlan{Gemm::wide, bm, bn, 1}); break;
+        case 5: if (k64) ALR_GEMM(256, 256, 2, 2, 64, 1); else ALR_GEMM(256, 256, 2, 2, 32, 1); break;
+        case 4: if (k64) ALR_GEMM(256, 256, 2, 4, 64, 1); else ALR_GEMM(256, 256, 2, 4, 32, 1); break;
+        case 1: if (k64) ALR_GEMM(256, 128, 2, 2, 64, 1); else ALR_GEMM(256, 128, 2, 2, 32, 1); break;
+        case 2: if (k64) ALR_GEMM(128, 128, 2, 2, 64, 2); else ALR_GEMM(128, 128, 2, 2, 32, 2); break;
+        default: if (k64) ALR_GEMM(64, 128, 2, 2, 64, 2); else ALR_GEMM(64, 128, 2, 2, 32, 4); break;
       }
-    }
-    switch (cfg) {
-      case 19:
-        gemm_bf16_pp64p_kernel<TAG, Epi>
-            <<<std::min(nb, ctx->n_cu), 512, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
-        break;
-      case 2: if (k64) ALR_GEMM(128, 128, 2, 2, 64, 2); else ALR_GEMM(128, 128, 2, 2, 32, 2); break;
-      default: if (k64) ALR_GEMM(64, 128, 2, 2, 64, 2); else ALR_GEMM(64, 128, 2, 2, 32, 4); break;
-    }
 #undef ALR_GEMM
+    }
   } else {
     const int tm = (M + GF_M - 1) / GF_M, tn = (N + GF_N - 1) / GF_N;
     gemm_f32_kernel<TAG, Epi><<<tm * tn, 256, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
