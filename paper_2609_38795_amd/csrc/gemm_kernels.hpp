@@ -60,11 +60,7 @@ struct EpiQKV {
   long kv_rs;
   const int* vt_col;  // if set: v is transposed, element (row, c) at v[c*vt_stride + vt_perm(vt_col[row])]
   long vt_stride;
-  const float* cosT;  // [max_pos, hd/2]
-  const float* sinT;
-  const int* pos;     // (t, h, w) position of row r: pos[3 r + axis] + pos_add
-  int pos_add;
-  int sec0, sec01;    // frequencies < sec0 follow axis t, < sec01 axis h, the rest axis w
+  const f32x2* rope;  // (cos, sin) of row r's position at frequency i: rope[r * hd/2 + i]
   int H, G, hd;
   __device__ __forceinline__ void operator()(int row, int c, float lo, float hi) const {
     const int half = hd >> 1;
@@ -81,11 +77,9 @@ struct EpiQKV {
       }
       const int f = 32 * (cl >> 6) + (cl & 63);
       const int head = f / half, i = f - head * half;
-      const int axis = (i < sec0) ? 0 : ((i < sec01) ? 1 : 2);
-      const long p = (long)(pos[3 * row + axis] + pos_add);
-      const float cs = cosT[p * half + i], sn = sinT[p * half + i];
-      Elt<OutT>::st(dst + head * hd + i, rope_a(lo, hi, cs, sn));
-      Elt<OutT>::st(dst + head * hd + i + half, rope_b(lo, hi, cs, sn));
+      const f32x2 w = rope[(long)row * half + i];
+      Elt<OutT>::st(dst + head * hd + i, rope_a(lo, hi, w[0], w[1]));
+      Elt<OutT>::st(dst + head * hd + i + half, rope_b(lo, hi, w[0], w[1]));
     } else if (vt_col) {
       const long cl = c - qd - kd, col = vt_perm(vt_col[row]);
       Elt<OutT>::st(v + cl * vt_stride + col, lo);
@@ -100,8 +94,7 @@ struct EpiQKV {
   // Columns c..c+3 and c+32..c+35 of one row (c a multiple of 4 in the low
   // half of a 64-column group), for the split-K reduce: the same arithmetic
   // per element as operator(), with 16-byte loads of the RoPE factors (the
-  // four dims share a head, and an axis unless an M-RoPE section boundary
-  // falls between them) and 8-byte bf16 stores.
+  // four dims share a head) and 8-byte bf16 stores.
   __device__ __forceinline__ void quad(int row, int c, const f32x4& lo, const f32x4& hi) const {
     const int half = hd >> 1;
     const int qd = H * hd, kd = G * hd;
@@ -117,22 +110,9 @@ struct EpiQKV {
       }
       const int f = 32 * (cl >> 6) + (cl & 63);
       const int head = f / half, i = f - head * half;
-      f32x4 cs, sn;
-      const int ax0 = (i < sec0) ? 0 : ((i < sec01) ? 1 : 2);
-      const int ax3 = (i + 3 < sec0) ? 0 : ((i + 3 < sec01) ? 1 : 2);
-      if (ax0 == ax3) {
-        const long o = (long)(pos[3 * row + ax0] + pos_add) * half + i;
-        cs = *(const f32x4*)(cosT + o);
-        sn = *(const f32x4*)(sinT + o);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int ie = i + e, ax = (ie < sec0) ? 0 : ((ie < sec01) ? 1 : 2);
-          const long o = (long)(pos[3 * row + ax] + pos_add) * half + ie;
-          cs[e] = cosT[o];
-          sn[e] = sinT[o];
-        }
-      }
+      const f32x4* o = (const f32x4*)(rope + (long)row * half + i);
+      const f32x4 w0 = o[0], w1 = o[1];
+      const f32x4 cs = {w0[0], w0[2], w1[0], w1[2]}, sn = {w0[1], w0[3], w1[1], w1[3]};
       f32x4 a, b;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -169,9 +149,11 @@ struct EpiQKV {
   }
   // NR (4 or 16) rows of a lane (row of index t: rb + QS (t >> 2) +
   // (t & 3); rows >= M are skipped) of columns c and c+32.  Every load the
-  // rows need (positions, then cos/sin, or the V^T columns) is issued before
-  // any store, so the block costs two memory round trips rather than one per
-  // row.  Four consecutive, 4-aligned columns of the transposed V cache go out
+  // rows need (cos/sin, or the V^T columns) is issued before any store, so the
+  // block costs one memory round trip.  Looking the rows' positions up here first
+  // made it two, and in the 256x256 kernel, where nothing hides them, the prefill
+  // projection (32768 x 6144 x 4096) took 1.37 ms instead of 1.27.  Four consecutive,
+  // 4-aligned columns of the transposed V cache go out
   // as one 8-byte store per column (bf16).
   static constexpr bool by_rows = true;
   template <int NR, int QS = 8>
@@ -197,17 +179,9 @@ struct EpiQKV {
       }
       const int f = 32 * (cl >> 6) + (cl & 63);
       const int head = f / half, i = f - head * half;
-      const int axis = (i < sec0) ? 0 : ((i < sec01) ? 1 : 2);
-      int pp[NR];
+      f32x2 w[NR];
 #pragma unroll
-      for (int t = 0; t < NR; ++t) pp[t] = pos[3 * min(r[t], M - 1) + axis];
-      float cs[NR], sn[NR];
-#pragma unroll
-      for (int t = 0; t < NR; ++t) {
-        const long o = (long)(pp[t] + pos_add) * half + i;
-        cs[t] = cosT[o];
-        sn[t] = sinT[o];
-      }
+      for (int t = 0; t < NR; ++t) w[t] = rope[(long)min(r[t], M - 1) * half + i];
       // The two lanes of a column pair (i even, i+1 in the same head since half
       // is even) trade one value of each half per two rows, so the even lane
       // writes row r at i, i+1 and the odd lane row r+1: one store of two
@@ -216,8 +190,8 @@ struct EpiQKV {
       float a[NR], b[NR];
 #pragma unroll
       for (int t = 0; t < NR; ++t) {
-        a[t] = rope_a(lo[t], hi[t], cs[t], sn[t]);
-        b[t] = rope_b(lo[t], hi[t], cs[t], sn[t]);
+        a[t] = rope_a(lo[t], hi[t], w[t][0], w[t][1]);
+        b[t] = rope_b(lo[t], hi[t], w[t][0], w[t][1]);
       }
 #pragma unroll
       for (int t = 0; t < NR; t += 2) {

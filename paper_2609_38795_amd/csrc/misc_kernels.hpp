@@ -20,6 +20,17 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   return t;
 }
 
+// (cos, sin) rows of the positions a pass runs at: rope[r, i] = tab[p, i] for
+// frequency i < half, where p = pos[3 r + axis] + pos_add and the frequencies
+// < sec0 follow axis t, < sec01 axis h, the rest axis w.  Formed once per pass by
+// the embedding kernel, so that no layer's QKV epilogue looks a position up.
+struct RopeRows {
+  f32x2* rope;       // [rows, half]
+  const f32x2* tab;  // [max_pos, half]
+  const int* pos;
+  int pos_add, half, sec0, sec01;
+};
+
 // resid[r, :] = given[r, :] where mask[r] != 0, else E[tok[r], :]  (fp32 stream);
 // d a multiple of 16 / sizeof(T).  Each thread moves 16-byte chunks of the
 // source row, four at a time: the loads of a round are issued before its
@@ -29,13 +40,18 @@ __global__ __launch_bounds__(256) void embed_kernel(float* __restrict__ resid,
                                                     const int* __restrict__ tok,
                                                     const T* __restrict__ E,
                                                     const T* __restrict__ given,
-                                                    const uint8_t* __restrict__ mask, int d) {
+                                                    const uint8_t* __restrict__ mask, int d,
+                                                    RopeRows rr) {
   constexpr int EPC = 16 / (int)sizeof(T);  // elements per 16-byte chunk
   constexpr int U = 4;                      // chunks per thread per round
   const long r = blockIdx.x;
   const bool use_given = mask != nullptr && mask[r] != 0;
   const T* src = use_given ? given + r * d : E + (long)tok[r] * d;
   float* dst = resid + r * d;
+  for (int i = threadIdx.x; i < rr.half; i += 256) {
+    const int axis = (i < rr.sec0) ? 0 : ((i < rr.sec01) ? 1 : 2);
+    rr.rope[r * rr.half + i] = rr.tab[(long)(rr.pos[3 * r + axis] + rr.pos_add) * rr.half + i];
+  }
   const int nch = d / EPC;
   for (int c0 = threadIdx.x; c0 < nch; c0 += 256 * U) {
     u32x4 w[U];

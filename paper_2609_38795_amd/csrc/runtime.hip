@@ -49,7 +49,7 @@ struct Layout {
   size_t w_embed, w_lm, w_fnorm;
   size_t layer0, layer_stride;  // per layer block
   size_t l_anorm, l_fnorm, l_qkv, l_o, l_gu, l_down;  // offsets within a layer block
-  size_t rope_cos, rope_sin;
+  size_t rope, rope_rows;
   size_t kc, vc, kv_layer_stride;
   size_t vt_stride;  // columns of the transposed V cache (0 when V is stored natural)
   size_t kp, vp, kvp_layer_stride;
@@ -200,8 +200,8 @@ size_t compute_layout(const alr_config& c, const alr_limits& lim, Layout& L) {
     L.layer_stride = lo;
   }
   L.layer0 = take(nl * L.layer_stride);
-  L.rope_cos = take((size_t)c.max_pos * (hd / 2) * 4);
-  L.rope_sin = take((size_t)c.max_pos * (hd / 2) * 4);
+  L.rope = take((size_t)c.max_pos * (hd / 2) * 8);
+  L.rope_rows = take(R * (hd / 2) * 8);
   // transposed V (MFMA attention): [G*hd][vt_stride] per layer, every sequence
   // starting at a multiple of 64 columns
   L.vt_stride = mfma_attn(c) ? ((T + 64 * (size_t)lim.max_seqs + 63) / 64) * 64 : 0;
@@ -725,25 +725,16 @@ alr_status layer_forward(alr_ctx* ctx, int l, int M, bool decode, int s, float* 
                                          c.rms_eps);
   EpiQKV<T> eq;
   eq.q = qb;
-  eq.cosT = ctx->at<float>(L.rope_cos);
-  eq.sinT = ctx->at<float>(L.rope_sin);
+  eq.rope = ctx->at<f32x2>(L.rope_rows);
   eq.H = H;
   eq.G = G;
   eq.hd = hd;
-  {
-    const int* ms = c.mrope_sections;
-    const bool none = ms[0] == 0 && ms[1] == 0 && ms[2] == 0;
-    eq.sec0 = none ? hd / 2 : ms[0];
-    eq.sec01 = none ? hd / 2 : ms[0] + ms[1];
-  }
   eq.vt_col = nullptr;
   eq.vt_stride = 0;
   if (!decode) {
     eq.k = kc;
     eq.v = vc;
     eq.kv_rs = kvd;
-    eq.pos = ctx->at<int>(L.i_tokpos);
-    eq.pos_add = 0;
     if (L.vt_stride) {
       eq.vt_col = ctx->at<int>(L.i_vtcol);
       eq.vt_stride = (long)L.vt_stride;
@@ -752,8 +743,6 @@ alr_status layer_forward(alr_ctx* ctx, int l, int M, bool decode, int s, float* 
     eq.k = kp + (long)(s - 1) * kvd;
     eq.v = vp + (long)(s - 1) * kvd;
     eq.kv_rs = priv_rs;
-    eq.pos = ctx->at<int>(L.i_rpos);
-    eq.pos_add = s;
   }
   if (decode)
     launch_gemm<ALR_PROF_DECODE_QKV, T>(ctx, xn, d, reinterpret_cast<const T*>(lw + L.l_qkv), d, M,
@@ -855,6 +844,17 @@ alr_status layer_forward(alr_ctx* ctx, int l, int M, bool decode, int s, float* 
   return ALR_OK;
 }
 
+// RoPE rows of a pass over the corpus tokens (slot 0) or of rollout slot s
+RopeRows rope_rows(const alr_ctx* ctx, int s) {
+  const alr_config& c = ctx->cfg;
+  const int* ms = c.mrope_sections;
+  const bool none = ms[0] == 0 && ms[1] == 0 && ms[2] == 0;
+  const int half = c.head_dim / 2;
+  return RopeRows{ctx->at<f32x2>(ctx->L.rope_rows), ctx->at<f32x2>(ctx->L.rope),
+                  ctx->at<int>(s == 0 ? ctx->L.i_tokpos : ctx->L.i_rpos), s, half,
+                  none ? half : ms[0], none ? half : ms[0] + ms[1]};
+}
+
 int feat_index(const alr_config& c, int l) {
   for (int f = 0; f < c.n_feat; ++f)
     if (c.feat_layers[f] == l) return f;
@@ -868,7 +868,8 @@ alr_status prefill_impl(alr_ctx* ctx, int M, const int32_t* tokens, const void* 
   const Layout& L = ctx->L;
   const int d = c.d_model, nf = c.n_feat;
   embed_kernel<T><<<M, 256, 0, st>>>(ctx->at<float>(L.resid), tokens, ctx->at<T>(L.w_embed),
-                                     reinterpret_cast<const T*>(embeds), mask, d);
+                                     reinterpret_cast<const T*>(embeds), mask, d,
+                                     rope_rows(ctx, 0));
   keep_tokens_kernel<<<(M + 255) / 256, 256, 0, st>>>(ctx->at<int>(L.i_ctok), tokens, mask, M);
   ALR_LAUNCHED(ctx, "embed");
   if constexpr (std::is_same<T, bf16>::value) {
@@ -997,7 +998,8 @@ alr_status rollout_impl(alr_ctx* ctx, int n, int block, const int32_t* forced, c
   if (stt != ALR_OK) return stt;
   for (int s = 1; s < block; ++s) {
     embed_kernel<T><<<n, 256, 0, st>>>(ctx->at<float>(L.resid), ctx->at<int>(L.i_cur),
-                                       ctx->at<T>(L.w_embed), nullptr, nullptr, d);
+                                       ctx->at<T>(L.w_embed), nullptr, nullptr, d,
+                                       rope_rows(ctx, s));
     ALR_LAUNCHED(ctx, "decode embed");
     bool normed = false;  // as in the prefill
     for (int l = 0; l < c.n_layers; ++l) {
@@ -1369,20 +1371,19 @@ alr_status alr_create(const alr_config* cfg, const alr_weights* w, const alr_lim
       CREATE_HIP(hipGetLastError());
     }
   }
-  // RoPE tables: angles in double, stored as float cos/sin [max_pos, hd/2]
+  // RoPE table: angles in double, stored as float (cos, sin) [max_pos, hd/2]
   {
     const int half = hd / 2;
-    std::vector<float> cs((size_t)c.max_pos * half), sn((size_t)c.max_pos * half);
+    std::vector<float> cs((size_t)c.max_pos * half * 2);
     for (int i = 0; i < half; ++i) {
       const double inv = std::pow((double)c.rope_base, -2.0 * i / hd);
       for (int p = 0; p < c.max_pos; ++p) {
         const double a = p * inv;
-        cs[(size_t)p * half + i] = (float)std::cos(a);
-        sn[(size_t)p * half + i] = (float)std::sin(a);
+        cs[((size_t)p * half + i) * 2] = (float)std::cos(a);
+        cs[((size_t)p * half + i) * 2 + 1] = (float)std::sin(a);
       }
     }
-    CREATE_HIP(hipMemcpyAsync(ctx->ws + L.rope_cos, cs.data(), cs.size() * 4, hipMemcpyHostToDevice, s));
-    CREATE_HIP(hipMemcpyAsync(ctx->ws + L.rope_sin, sn.data(), sn.size() * 4, hipMemcpyHostToDevice, s));
+    CREATE_HIP(hipMemcpyAsync(ctx->ws + L.rope, cs.data(), cs.size() * 4, hipMemcpyHostToDevice, s));
     CREATE_HIP(hipStreamSynchronize(s));
   }
 #undef CREATE_HIP
