@@ -20,83 +20,145 @@ struct AttnGeom {
 };
 
 // ------------------------------------------------------------------ generic kernel
-// One wave per (query row, head); lanes over keys for the scores, lanes over
-// dimensions for the weighted sum.  Handles any even hd <= 256.  Used for the
-// fp32 path and for head sizes the MFMA kernels do not cover.
+// One workgroup per (query row, head), its four waves taking 64-key tiles in
+// turn and merging their softmax states at the end.  Scores: a lane per key.
+// Weighted sum: lanes over VEC dimensions each, the wave's remaining lanes over
+// keys.  Handles any even hd <= 256 (VEC = 2; whole 16-byte loads where hd is a
+// multiple of their elements).  Used for the fp32 path and for head sizes the
+// MFMA kernels do not cover.
+// What bounds it at the sizes it is used for (8 .. 600 rows of a few hundred keys)
+// is the chain of memory round trips: one wave over all keys of a row, one
+// key after the other, took 32 us at 128 rows x 4 heads, hd 32; a tile's key and
+// value rows are now all loaded before the first score (5.8 us).
 //   prefill (priv == nullptr): row r is corpus token r, sequence start
 //     row_start[r]; it sees shared rows row_start[r] .. r.
 //   decode: row r is sorted anchor r with shared rows tok0[r] .. tok0[r] +
 //     apos[r] where tok0[r] is its sequence start, then n_priv private slots.
-template <typename T>
+template <typename T, int N>
+struct alignas(sizeof(T) * N) EltVec {
+  T v[N];
+};
+
+template <typename T, int VEC>
 __global__ __launch_bounds__(256) void attn_generic_kernel(
     const T* __restrict__ Q, const T* __restrict__ Kc, const T* __restrict__ Vc,
     const T* __restrict__ Kp, const T* __restrict__ Vp, long priv_rs, int n_priv,
     const int* __restrict__ row_start, const int* __restrict__ apos, T* __restrict__ O,
     int n_rows, AttnGeom g) {
-  __shared__ float qs[4][256];
+  using V = EltVec<T, VEC>;
+  constexpr int NC = (256 / VEC + 63) / 64;  // VEC-runs of dimensions per lane
+  __shared__ float qs[256];
+  __shared__ float ps[4][64];
+  __shared__ float ms[4], ls[4];
+  __shared__ float os[4][256];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const long item_raw = (long)blockIdx.x * 4 + wave;
-  const bool valid = item_raw < (long)n_rows * g.H;
-  const long item = valid ? item_raw : 0;
-  const int row = (int)(item / g.H), head = (int)(item % g.H);
+  const int row = (int)(blockIdx.x / g.H), head = (int)(blockIdx.x % g.H);
   const int kvh = head / (g.H / g.G);
   const int hd = g.hd;
   const long kv_rs = (long)g.G * hd;
-  const T* q = Q + (long)row * g.H * hd + (long)head * hd;
-  for (int d = lane; d < hd; d += 64) qs[wave][d] = Elt<T>::ld(q + d);
+  if ((int)threadIdx.x < hd)
+    qs[threadIdx.x] = Elt<T>::ld(Q + ((long)row * g.H + head) * hd + threadIdx.x);
   __syncthreads();
-  if (!valid) return;
-  int first, n_shared, n_total;
-  if (Kp == nullptr) {
-    first = row_start[row];
-    n_shared = row - first + 1;
-    n_total = n_shared;
-  } else {
-    first = row_start[row];
-    n_shared = apos[row] + 1;
-    n_total = n_shared + n_priv;
-  }
+  const int first = row_start[row];
+  const int n_shared = (Kp == nullptr) ? row - first + 1 : apos[row] + 1;
+  const int n_total = (Kp == nullptr) ? n_shared : n_shared + n_priv;
+  const T* ksh = Kc + (long)first * kv_rs + (long)kvh * hd;
+  const T* vsh = Vc + (long)first * kv_rs + (long)kvh * hd;
+  const T* kpr = Kp + (long)row * priv_rs + (long)kvh * hd;
+  const T* vpr = Vp + (long)row * priv_rs + (long)kvh * hd;
+  auto key_row = [&](const T* sh, const T* pr, int j) {
+    return j < n_shared ? sh + (long)j * kv_rs : pr + (long)(j - n_shared) * kv_rs;
+  };
+  // runs of VEC dimensions per key, the lanes that share a key (a power of two)
+  // and the keys a pass of the wave covers
+  const int runs = hd / VEC;
+  int lpk = 1;
+  while (lpk < min(runs, 64)) lpk *= 2;
+  const int kpp = 64 / lpk, sub = lane / lpk, run0 = lane % lpk;
   float m = -INFINITY, l = 0.f;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int j0 = 0; j0 < n_total; j0 += 64) {
-    const int j = j0 + lane;
-    float sc = -INFINITY;
-    if (j < n_total) {
-      const T* kp = (j < n_shared) ? Kc + (long)(first + j) * kv_rs + (long)kvh * hd
-                                   : Kp + (long)row * priv_rs + (long)(j - n_shared) * kv_rs +
-                                         (long)kvh * hd;
-      float dot = 0.f;
-      for (int d = 0; d < hd; ++d) dot = fmaf(qs[wave][d], Elt<T>::ld(kp + d), dot);
-      sc = dot * g.scale_log2;
+  float acc[NC][VEC];
+#pragma unroll
+  for (int i = 0; i < NC; ++i)
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) acc[i][e] = 0.f;
+  for (int j0 = wave * 64; j0 < n_total; j0 += 256) {
+    const int j = j0 + lane, jl = n_total - 1;
+    const T* kp = key_row(ksh, kpr, min(j, jl));
+    // the first eight passes' value rows are on their way while the scores form
+    V pre[NC][8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const T* vp = key_row(vsh, vpr, min(j0 + t * kpp + sub, jl));
+#pragma unroll
+      for (int i = 0; i < NC; ++i)
+        pre[i][t] = *(const V*)(vp + min(run0 + 64 * i, runs - 1) * VEC);
     }
+    float dot = 0.f;
+#pragma unroll 8
+    for (int d = 0; d < runs; ++d) {
+      const V kv = *(const V*)(kp + d * VEC);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) dot = fmaf(qs[d * VEC + e], Elt<T>::ld(&kv.v[e]), dot);
+    }
+    const float sc = (j < n_total) ? dot * g.scale_log2 : -INFINITY;
     const float m_new = fmaxf(m, wave_max(sc));
     const float alpha = fast_exp2(m - m_new);
     const float p = (j < n_total) ? fast_exp2(sc - m_new) : 0.f;
     l = l * alpha + wave_sum(p);
+    ps[wave][lane] = p;  // read back by this wave alone
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] *= alpha;
+    for (int i = 0; i < NC; ++i)
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) acc[i][e] *= alpha;
     const int cnt = min(64, n_total - j0);
-    for (int jj = 0; jj < cnt; ++jj) {
-      const float pj = __shfl(p, jj);
-      const int jk = j0 + jj;
-      const T* vp = (jk < n_shared) ? Vc + (long)(first + jk) * kv_rs + (long)kvh * hd
-                                    : Vp + (long)row * priv_rs + (long)(jk - n_shared) * kv_rs +
-                                          (long)kvh * hd;
+    auto add = [&](int jj, int i, const V& vv) {
+      const float pj = ps[wave][jj];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int d = lane + 64 * i;
-        if (d < hd) acc[i] = fmaf(pj, Elt<T>::ld(vp + d), acc[i]);
-      }
+      for (int e = 0; e < VEC; ++e) acc[i][e] = fmaf(pj, Elt<T>::ld(&vv.v[e]), acc[i][e]);
+    };
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+      if (t * kpp + sub < cnt)
+#pragma unroll
+        for (int i = 0; i < NC; ++i) add(t * kpp + sub, i, pre[i][t]);
+#pragma unroll 4
+    for (int jj = 8 * kpp + sub; jj < cnt; jj += kpp) {
+      const T* vp = key_row(vsh, vpr, j0 + jj);
+#pragma unroll
+      for (int i = 0; i < NC; ++i)
+        add(jj, i, *(const V*)(vp + min(run0 + 64 * i, runs - 1) * VEC));
     }
     m = m_new;
   }
-  T* o = O + (long)row * g.H * hd + (long)head * hd;
-  const float inv = 1.f / l;
+  // over the lanes that held the same dimensions of other keys, then over the waves
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int d = lane + 64 * i;
-    if (d < hd) Elt<T>::st(o + d, acc[i] * inv);
+  for (int i = 0; i < NC; ++i)
+#pragma unroll
+    for (int e = 0; e < VEC; ++e)
+      for (int off = lpk; off < 64; off *= 2) acc[i][e] += __shfl_xor(acc[i][e], off);
+  if (sub == 0) {
+#pragma unroll
+    for (int i = 0; i < NC; ++i)
+      if (run0 + 64 * i < runs)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) os[wave][(run0 + 64 * i) * VEC + e] = acc[i][e];
   }
+  if (lane == 0) {
+    ms[wave] = m;
+    ls[wave] = l;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x >= hd) return;
+  // wave 0 always had keys; a wave without any has l = 0 and adds nothing
+  const float mm = fmaxf(fmaxf(ms[0], ms[1]), fmaxf(ms[2], ms[3]));
+  float lt = 0.f, ot = 0.f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const float f = ls[w] == 0.f ? 0.f : fast_exp2(ms[w] - mm);
+    lt = fmaf(f, ls[w], lt);
+    ot = fmaf(f, os[w][threadIdx.x], ot);
+  }
+  Elt<T>::st(O + ((long)row * g.H + head) * hd + threadIdx.x, ot / lt);
 }
 
 // ------------------------------------------------------------------ MFMA kernels (bf16)

@@ -667,7 +667,16 @@ void launch_gemm(alr_ctx* ctx, const T* A, int lda, const T* W, int ldw, int M, 
     }
   } else {
     const int tm = (M + GF_M - 1) / GF_M, tn = (N + GF_N - 1) / GF_N;
-    gemm_f32_kernel<TAG, Epi><<<tm * tn, 256, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
+    // 64x64 tiles pay where they fill the CUs (M = 1200, N = 1024, K = 128: 304 tiles)
+    if (tm * tn >= ctx->n_cu) {
+      gemm_f32_kernel<TAG, Epi><<<tm * tn, 256, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
+    } else {
+      const dim3 grid(N / 64, (M + GFS_M - 1) / GFS_M);
+      if (K >= 256)
+        gemm_f32_small_kernel<TAG, 16, Epi><<<grid, 1024, 0, st>>>(A, lda, W, ldw, M, N, K, epi);
+      else
+        gemm_f32_small_kernel<TAG, 8, Epi><<<grid, 512, 0, st>>>(A, lda, W, ldw, M, N, K, epi);
+    }
   }
 }
 
@@ -678,6 +687,21 @@ AttnGeom geom(const alr_config& c) {
   g.hd = c.head_dim;
   g.scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)c.head_dim));
   return g;
+}
+
+// Whole 16-byte loads of key and value rows where every row starts on one.
+template <typename T>
+void launch_attn_generic(const T* q, const T* kc, const T* vc, const T* kp, const T* vp,
+                         long priv_rs, int n_priv, const int* row_start, const int* apos, T* out,
+                         int rows, const AttnGeom& g, hipStream_t st) {
+  constexpr int VEC = 16 / (int)sizeof(T);
+  const unsigned grid = (unsigned)((long)rows * g.H);
+  if (g.hd % VEC == 0)
+    attn_generic_kernel<T, VEC><<<grid, 256, 0, st>>>(q, kc, vc, kp, vp, priv_rs, n_priv,
+                                                      row_start, apos, out, rows, g);
+  else
+    attn_generic_kernel<T, 2><<<grid, 256, 0, st>>>(q, kc, vc, kp, vp, priv_rs, n_priv, row_start,
+                                                    apos, out, rows, g);
 }
 
 // Column arrangement of the fused QKV weight: for q (n heads of hd), the
@@ -768,9 +792,8 @@ alr_status layer_forward(alr_ctx* ctx, int l, int M, bool decode, int s, float* 
               <<<nw, 256, 0, st>>>(qb, kc, vc, (long)L.vt_stride, at, wk, g);
       }
     } else {
-      const long items = (long)M * H;
-      attn_generic_kernel<T><<<(unsigned)((items + 3) / 4), 256, 0, st>>>(
-          qb, kc, vc, nullptr, nullptr, 0, 0, ctx->at<int>(L.i_rowstart), nullptr, at, M, g);
+      launch_attn_generic<T>(qb, kc, vc, nullptr, nullptr, 0, 0, ctx->at<int>(L.i_rowstart),
+                             nullptr, at, M, g, st);
     }
   } else {
     if (mfma_attn(c)) {
@@ -796,10 +819,8 @@ alr_status layer_forward(alr_ctx* ctx, int l, int M, bool decode, int s, float* 
         }
       }
     } else {
-      const long items = (long)M * H;
-      attn_generic_kernel<T><<<(unsigned)((items + 3) / 4), 256, 0, st>>>(
-          qb, kc, vc, kp, vp, priv_rs, s, ctx->at<int>(L.i_aseq), ctx->at<int>(L.i_apos), at, M,
-          g);
+      launch_attn_generic<T>(qb, kc, vc, kp, vp, priv_rs, s, ctx->at<int>(L.i_aseq),
+                             ctx->at<int>(L.i_apos), at, M, g, st);
     }
   }
   }

@@ -79,6 +79,19 @@ def test_gemm_wide(M, N, K, tile):
     assert err <= 2e-5 * np.sqrt(K) * 4, err
 
 
+@pytest.mark.parametrize("M,N,K", [(7, 64, 64), (8, 128, 512), (9, 192, 320), (4097, 256, 64)])
+def test_gemm_f32_few_tiles(M, N, K):
+    """fp32 products around the 8-row tiles of the kernel whose waves share K (one wave with work,
+    K not a multiple of the waves' share), and the first size that goes to 64x64 tiles on 256 CUs."""
+    _print(f"gemm f32 {M}x{N}x{K}")
+    g = torch.Generator().manual_seed(M + K)
+    a, w = (torch.randn(s, generator=g).cuda() for s in ((M, K), (N, K)))
+    c = torch.full((M, N), float("nan"), device="cuda")
+    binding.debug_gemm(binding.ALR_F32, a, w, c)
+    err = (c.double() - a.double() @ w.double().T).abs().max().item()
+    assert err <= 2e-5 * np.sqrt(K) * 4, err
+
+
 def test_rollout_batches_agree():
     """The first n anchors rolled out alone (ring kernels, each row tile, split and unsplit)
     against the same anchors in a batch of 257 (the tiled kernels), on forced tokens."""
@@ -152,6 +165,30 @@ def test_small_bf16_attention_paths(hd, H, G):
                    W.random_tokens(2048, (2, 300), 9, dist="zipf"),
                    *W.random_anchors(2, 300, 6, 0, 299, 4), None, None)
     rep = _full_compare(inp)
+    assert rep.ok()
+
+
+@pytest.mark.parametrize("dtype,hd,H,G", [("f32", 96, 4, 2), ("f32", 250, 32, 32), ("bf16", 80, 8, 4),
+                                          ("bf16", 36, 32, 16)])
+def test_generic_attention_head_sizes(dtype, hd, H, G):
+    """The generic attention with 16-byte loads at head sizes that leave lanes of a key idle (96,
+    80), with 4- and 8-byte ones where rows do not start on 16 bytes (36 in bf16, 250), rows of
+    more keys than one round of its four waves, and a one-key prefix."""
+    base = W.get("small_bf16")
+    lens = [300, 1]
+    w = W.scaled(base, f"generic_{dtype}_{hd}", n_layers=2, d_model=256, n_heads=H, n_kv_heads=G,
+                 head_dim=hd, d_ffn=128, vocab=512, feat_layers=(0, 1), dtype=dtype, n_seq=2,
+                 seq_len=300, block=4)
+    tok = W.random_tokens(512, (2, 300), hd, dist="zipf")
+    a_seq, a_pos = np.array([0, 0, 0, 0, 1], np.int32), np.array([0, 63, 254, 299, 0], np.int32)
+    inp = W.Inputs(w, W.random_weights(w.shape, hd, scale=0.05, norm_gain="random"), tok, a_seq,
+                   a_pos, None, None)
+    eng = make_engine(inp, max_anchors=5, max_block=4)
+    flat = np.concatenate([tok[s, :n] for s, n in enumerate(lens)]).astype(np.int32)
+    eng.prefill(torch.from_numpy(flat).to(eng.device), lens)
+    rep = compare(inp, w.shape, np.arange(5), runner(eng, a_seq, a_pos, 4), 4)
+    eng.close()
+    _print(rep)
     assert rep.ok()
 
 
