@@ -27,13 +27,14 @@ extern "C" {
  * (K slices of at least 192 summed in slice order by a second kernel; 2 or 4
  * slices, the unsplit kernel when K allows none); 19 = the kernel of 17 run
  * persistently (one workgroup per CU looping over the tiles, the next tile's
- * first K steps copied during the current tile's epilogue); 17 to 19 run as 3
- * when K < 192; 20 = split-K
- * over the 64x128 kernel of 3 (2 or 4 slices, each a multiple of 64; the
- * unsplit kernel of 3 when K allows no split).  Other values:
- * ALR_E_INVALID_ARG.  Tiles 18 and 20 need a device scratch buffer of at
- * least 2*M*N*4 bytes for the partial sums (up to 4*M*N*4 are used when
- * given); ALR_E_WORKSPACE otherwise.
+ * first K steps copied during the current tile's epilogue); 20 = split-K over the
+ * 64x128 kernel of 3 (2 or 4 slices, each a multiple of 64; the unsplit kernel of
+ * 3 when K allows no split); 21 = 19 with the tiles past the last full round of
+ * one tile per CU cut over K, into as many slices (of at least 192) as idle CUs
+ * and the scratch (256 KB a slice of a tile) allow.  17 to 19 and 21 run as 3
+ * when K < 192.  Other values: ALR_E_INVALID_ARG.  Tiles 18 and 20 need a device
+ * scratch buffer of at least 2*M*N*4 bytes for the partial sums (up to 4*M*N*4
+ * are used when given), tile 21 one of any size; ALR_E_WORKSPACE otherwise.
  * Enqueued on `stream`. */
 alr_status alr_debug_gemm(int32_t dtype, const void* A, const void* W, float* C, int32_t M,
                           int32_t N, int32_t K, int32_t tile, void* scratch,

@@ -450,6 +450,9 @@ def debug_gemm(dtype: int, A, W, C, stream=None, tile: int = 0):
     nbytes = 0
     if dtype == ALR_BF16 and tile in (18, 20):
         nbytes = 4 * M * N * 4
+    if dtype == ALR_BF16 and tile == 21:
+        nbytes = 64 << 20  # a 256x256 partial tile per CU
+    if nbytes:
         scratch = torch.empty(nbytes, dtype=torch.uint8, device=A.device)
     st = lib.alr_debug_gemm(dtype, A.data_ptr(), W.data_ptr(), C.data_ptr(), M, N, K, tile,
                             None if scratch is None else scratch.data_ptr(), nbytes,

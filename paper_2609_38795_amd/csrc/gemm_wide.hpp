@@ -137,19 +137,50 @@ __device__ __forceinline__ void wide_store_tile(const Epi& epi, const f32x16 (&a
   }
 }
 
-// Workgroup b takes units b, b + gridDim.x, ...; with splits > 1 unit u is K slice
-// u % splits (of K columns, for an epilogue with set_split) of tile u / splits.
-// K >= 192 and a multiple of 64.  The first two K steps of the next unit are
-// copied while this one's epilogue runs.
+// Part of a product: tiles first .. first + count - 1 of its tile order, each cut into
+// `splits` slices of (nearly) equal runs of K steps where the epilogue takes raw sums.
+struct WideTiles {
+  int first, count, splits;
+};
+
+// Raw sums of the slices of the tiles past the last full round, for
+// gemm_wide_tail_kernel: part[unit][256][256].
+struct EpiTail {
+  float* part;
+  __device__ __forceinline__ void set_unit(int unit, int tm, int tn) {
+    part += ((long)unit - tm) * 65536 - tn * 256;
+  }
+  __device__ __forceinline__ void operator()(int row, int c, float lo, float hi) const {
+    part[(long)row * 256 + c] = lo;
+    part[(long)row * 256 + c + 32] = hi;
+  }
+};
+
+template <class Epi, class = void>
+struct has_set_unit : std::false_type {};
+template <class Epi>
+struct has_set_unit<Epi, decltype((void)&Epi::set_unit)> : std::true_type {};
+
+// Workgroup b takes units b, b + gridDim.x, ...; unit u is slice u % splits of tile
+// u / splits of the part.  K is a multiple of 64 and every unit has at least three K
+// steps.  The first two K steps of the next unit are copied while this one's epilogue
+// runs.
+//
+// A last round with few tiles costs most of a full one: the down projection of 10,900
+// rows (N = 3584, K = 18944) is 602 tiles, 2.35 rounds of 400 us, and took 1.45 ms.  Its
+// 90 tiles past the second round are cut over K, 2 slices each, by a second launch,
+// and summed by a third: 0.90 + 0.21 + 0.02 ms.  Slicing them inside the first launch
+// cost every epilogue registers (spills in SwiGLU's).
 template <int TAG, class Epi>
 __global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(
     const bf16* __restrict__ A, int lda, const bf16* __restrict__ W, int ldw, int M, int N, int K,
-    int tiles_m, int tiles_n, Epi epi, int splits) {
+    int tiles_m, int tiles_n, Epi epi, WideTiles wt) {
+  constexpr bool sliced = has_set_split<Epi>::value || has_set_unit<Epi>::value;
   constexpr int BM = 256, BN = 256, BK = 64;
   // two stages of [A tile | W tile], rows of 128 bytes swizzled as swz<64>; the
   // stages are 64 KB apart and told apart by that address bit alone
   __shared__ __attribute__((aligned(65536))) bf16 smem[2 * (BM + BN) * BK];
-  const int units = tiles_m * tiles_n * splits;
+  const int units = sliced ? wt.count * wt.splits : wt.count;
   int unit = blockIdx.x;
   if (unit >= units) return;  // uniform over the workgroup
   const int lane = threadIdx.x & 63, r16 = lane & 15;
@@ -165,12 +196,19 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(
   }
   u32x16 vo;
   const bf16 *ga, *gw;
-  int tm, tn;
-  // offsets of a unit's tile and the copies of its first two steps
+  int tm, tn, steps = K / BK;
+  // K steps and tile offsets of a unit, and the copies of its first two steps
   auto begin = [&](int u) {
-    gemm_tile_coords(u / splits, tiles_m, tiles_n, tm, tn);
-    ga = A + (long)(u % splits) * K;
-    gw = W + (long)(u % splits) * K;
+    int tile = wt.first + u, first = 0;
+    if constexpr (sliced) {
+      const int t = u / wt.splits, sl = u - t * wt.splits;
+      tile = wt.first + t;
+      first = K / BK * sl / wt.splits;
+      steps = K / BK * (sl + 1) / wt.splits - first;
+    }
+    gemm_tile_coords(tile, tiles_m, tiles_n, tm, tn);
+    ga = A + (long)first * BK;
+    gw = W + (long)first * BK;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int r = 8 * (j * 4 + wave) + (lane >> 3);
@@ -193,7 +231,7 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(
   while (true) {
     const int m0 = tm * BM + wm * 128, n0 = tn * BN + wn * 128;
     f32x16 acc[16];
-    int n = K / BK - 2;  // steps that refill their stage
+    int n = steps - 2;  // steps that refill their stage
     uint32_t ldsc = ldsw;
     u32x4 rda = rd;
 #pragma clang diagnostic push
@@ -246,13 +284,51 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(
     unit += gridDim.x;
     const bool more = unit < units;
     Epi e = epi;
-    if constexpr (has_set_split<Epi>::value) e.set_split((unit - (int)gridDim.x) % splits);
+    if constexpr (has_set_split<Epi>::value) e.set_split((unit - (int)gridDim.x) % wt.splits);
+    if constexpr (has_set_unit<Epi>::value) e.set_unit(unit - (int)gridDim.x, tm, tn);
     if (more) begin(unit);
     // Before the last quarter of the epilogue the next unit's copies have
     // landed, so its first reads need not wait for the stores that remain.
     wide_store_tile(e, acc, m0, n0, M, N,
                     [] { __builtin_amdgcn_s_waitcnt((0x7 << 4) | (0xF << 8)); });
     if (!more) break;
+  }
+}
+
+// Sum, in slice order, and epilogue of the tiles that were cut over K: workgroup
+// (t, b) takes rows 16 b .. + 15 of tile first + t, half-wave w of it the 64-column
+// group w % 4 of rows 4 (w / 4) .. + 3 and those + 8.  All 16 loads of a slice are
+// independent; bound by reading the partial sums (256 KB a unit).
+template <class Epi>
+__global__ __launch_bounds__(256) void gemm_wide_tail_kernel(int M, int N, int tiles_m, int tiles_n,
+                                                             Epi epi, WideTiles wt,
+                                                             const float* __restrict__ part) {
+  int tm, tn;
+  gemm_tile_coords(wt.first + (int)blockIdx.x, tiles_m, tiles_n, tm, tn);
+  const int lc = threadIdx.x & 31, w = threadIdx.x >> 5;
+  const int r0 = 16 * blockIdx.y + 4 * (w >> 2), c0 = 64 * (w & 3) + lc;
+  const int rb = tm * 256 + r0, col = tn * 256 + c0;
+  if (col >= N || rb >= M) return;  // the same for a whole half-wave
+  const float* p = part + (long)blockIdx.x * wt.splits * 65536 + r0 * 256 + c0;
+  float lo[8], hi[8];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) lo[t] = hi[t] = 0.f;
+#pragma unroll 2
+  for (int sl = 0; sl < wt.splits; ++sl)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {  // rows past M hold whatever was there, and are not stored
+      const float* q = p + (long)sl * 65536 + (8 * (t >> 2) + (t & 3)) * 256;
+      lo[t] += q[0];
+      hi[t] += q[32];
+    }
+  if constexpr (has_rows<Epi>::value) {
+    epi.template rows<8>(rb, M, col, lo, hi);
+  } else {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int r = rb + 8 * (t >> 2) + (t & 3);
+      if (r < M) epi(r, col, lo[t], hi[t]);
+    }
   }
 }
 

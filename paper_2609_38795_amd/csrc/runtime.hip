@@ -157,6 +157,8 @@ alr_status check_operand_sizes(const alr_config& c, const alr_limits& lim, char*
   return ALR_OK;
 }
 
+// Partial sums of one 256x256 tile.
+constexpr size_t WIDE_PART_BYTES = 256 * 256 * 4;
 // Up to this many rows a product may be cut into 8 K slices (pick_gemm).
 constexpr int FEW_ROWS = 256;
 
@@ -508,10 +510,15 @@ enum class Gemm { ring32, ring64, ring128x64, ring128, lds128, wide };
 struct GemmPlan {
   Gemm kernel;
   int bm, bn, splits;
+  int tail = 1;  // K slices of the tiles past the last full round (256x256 only)
 };
+// Where the unsliced 256x256 kernel leaves half of the CUs or more idle in its last
+// round, the tiles of that round are cut over K (gemm_wide_tail_kernel) if the estimate
+// gains 10 us by it: a shorter round against the partial sums and two more launches.
 //   epi_us: what the unsliced 256x256 kernel's epilogue takes beyond plain stores.
+//   tail_bytes: scratch for the partial sums of the last round.
 GemmPlan pick_gemm(int M, int N, int K, int n_cu, size_t split_bytes, bool norm_follows,
-                   float epi_us) {
+                   float epi_us, size_t tail_bytes) {
   struct Kern {
     Gemm k;
     int bm, bn;
@@ -539,8 +546,23 @@ GemmPlan pick_gemm(int M, int N, int K, int n_cu, size_t split_bytes, bool norm_
       float us = (float)rounds * ((float)(K / 64 / S) * step + k.tile_us +
                                   (k.k == Gemm::wide && S == 1 ? epi_us : 0.f));
       if (S > 1) us += (float)S * M * N * (4.f / 4.2e6f) + (norm_follows ? 0.f : 3.f);
+      int tail = 1;
+      const long left = t % n_cu;
+      if (k.k == Gemm::wide && S == 1 && t > n_cu && 2 * left <= n_cu && left > 0) {
+        const int cut = (int)std::min({(long)n_cu / left, (long)K / 192,
+                                       (long)(tail_bytes / WIDE_PART_BYTES) / left});
+        auto step_at = [&](long units) { return 0.7f + 0.65f * (float)units / (float)n_cu; };
+        const float plain = (float)(K / 64) * step_at(left) + epi_us;
+        const float sliced = cut < 2 ? plain
+                                     : (float)(K / 64 / cut + 1) * step_at(left * cut) + 12.f +
+                                           (float)(left * cut) * (WIDE_PART_BYTES / 4.2e6f);
+        if (sliced + 10.f < plain) {
+          tail = cut;
+          us -= plain - sliced;
+        }
+      }
       if (best.splits == 0 || us < best_us) {
-        best = GemmPlan{k.k, k.bm, k.bn, S};
+        best = GemmPlan{k.k, k.bm, k.bn, S, tail};
         best_us = us;
       }
     }
@@ -550,7 +572,7 @@ GemmPlan pick_gemm(int M, int N, int K, int n_cu, size_t split_bytes, bool norm_
 
 template <int TAG, class Epi>
 void launch_plan(const GemmPlan& p, int n_cu, const bf16* A, int lda, const bf16* W, int ldw,
-                 int M, int N, int K, const Epi& epi, hipStream_t st) {
+                 int M, int N, int K, const Epi& epi, hipStream_t st, float* tail_buf) {
   const int tm = (M + p.bm - 1) / p.bm, tn = (N + p.bn - 1) / p.bn;
   const unsigned grid = (unsigned)((tn * p.splits + 7) / 8 * 8 * tm);
   const int Ks = K / p.splits;
@@ -572,12 +594,35 @@ void launch_plan(const GemmPlan& p, int n_cu, const bf16* A, int lda, const bf16
               <<<tm * tn, 256, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
       }
       break;
-    case Gemm::wide:
-      gemm_bf16_wide_kernel<TAG, Epi><<<std::min(tm * tn * p.splits, n_cu), 256, 0, st>>>(
-          A, lda, W, ldw, M, N, Ks, tm, tn, epi, p.splits);
+    case Gemm::wide: {
+      const int nt = tm * tn, left = p.tail > 1 ? nt % n_cu : 0;
+      const WideTiles main{0, nt - left, p.splits}, rest{nt - left, left, p.tail};
+      gemm_bf16_wide_kernel<TAG, Epi><<<std::min(main.count * main.splits, n_cu), 256, 0, st>>>(
+          A, lda, W, ldw, M, N, K, tm, tn, epi, main);
+      if constexpr (!has_set_split<Epi>::value)
+        if (left > 0) {
+          gemm_bf16_wide_kernel<0, EpiTail><<<left * p.tail, 256, 0, st>>>(
+              A, lda, W, ldw, M, N, K, tm, tn, EpiTail{tail_buf}, rest);
+          gemm_wide_tail_kernel<Epi>
+              <<<dim3(left, 16), 256, 0, st>>>(M, N, tm, tn, epi, rest, tail_buf);
+        }
       break;
+    }
   }
 #undef ALR_RING
+}
+
+// Where a product may leave partial sums besides splitk_buf: the activation buffers
+// that hold nothing at its site.  Before the MLP that is the one for the gate's and up's
+// product, from there on (and at the output head) the query and attention rows.
+template <int TAG>
+std::pair<float*, size_t> tail_scratch(const alr_ctx* ctx) {
+  const Layout& L = ctx->L;
+  if (TAG == 0) return {ctx->splitk_buf, ctx->splitk_bytes};
+  if (TAG == ALR_PROF_PREFILL_QKV || TAG == ALR_PROF_DECODE_QKV || TAG == ALR_PROF_PREFILL_O ||
+      TAG == ALR_PROF_DECODE_O)
+    return {ctx->at<float>(L.act), L.i_tokpos - L.act};
+  return {ctx->at<float>(L.qbuf), L.act - L.qbuf};
 }
 
 // norm_g / norm_out / normed: the RMSNorm that follows a residual update
@@ -595,13 +640,14 @@ void launch_gemm(alr_ctx* ctx, const T* A, int lda, const T* W, int ldw, int M, 
     bool epi_whole_k = false;
     if constexpr (std::is_same<Epi, EpiLogits>::value) epi_whole_k = epi.part != nullptr;
     const bool may_split = ctx->splitk_buf != nullptr && !epi_whole_k;
+    const std::pair<float*, size_t> tail = tail_scratch<TAG>(ctx);
     auto run = [&](const GemmPlan& p) {
       if (p.splits == 1) {
-        launch_plan<TAG>(p, ctx->n_cu, A, lda, W, ldw, M, N, K, epi, st);
+        launch_plan<TAG>(p, ctx->n_cu, A, lda, W, ldw, M, N, K, epi, st, tail.first);
         return;
       }
       launch_plan<TAG>(p, ctx->n_cu, A, lda, W, ldw, M, N, K,
-                       EpiPartial{ctx->splitk_buf, (long)M * N, N}, st);
+                       EpiPartial{ctx->splitk_buf, (long)M * N, N}, st, nullptr);
       if constexpr (std::is_same<Epi, EpiResid>::value) {
         if (norm_out && normed &&
             launch_splitk_resid_norm<T>(ctx, p.splits, M, N, epi, norm_g, norm_out, st)) {
@@ -614,7 +660,8 @@ void launch_gemm(alr_ctx* ctx, const T* A, int lda, const T* W, int ldw, int M, 
     if (force_tile == 0) {
       // all CUs reach their epilogues together, with nothing to hide loads behind
       const float epi_us = has_rows<Epi>::value && !std::is_same<Epi, EpiSwiGLU<bf16>>::value ? 14.f : 0.f;
-      run(pick_gemm(M, N, K, ctx->n_cu, may_split ? ctx->splitk_bytes : 0, norm_out != nullptr, epi_us));
+      run(pick_gemm(M, N, K, ctx->n_cu, may_split ? ctx->splitk_bytes : 0, norm_out != nullptr, epi_us,
+                    tail.second));
       return;
     }
     if constexpr (TAG == 0) {  // the debug hook's variants
@@ -654,8 +701,18 @@ void launch_gemm(alr_ctx* ctx, const T* A, int lda, const T* W, int ldw, int M, 
       <<<nb, 64 * WGM_ * WGN_, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi)
       switch (cfg) {
         case 17:
-          gemm_bf16_wide_kernel<TAG, Epi><<<nb, 256, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi, 1);
+          gemm_bf16_wide_kernel<TAG, Epi><<<nb, 256, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi,
+                                                              WideTiles{0, nb, 1});
           break;
+        case 21: {  // as many slices as the last round's idle CUs, K and the scratch allow
+          const long left = nb % ctx->n_cu;
+          GemmPlan p{Gemm::wide, bm, bn, 1};
+          if (nb > ctx->n_cu && left > 0)
+            p.tail = (int)std::min({(long)ctx->n_cu / left, (long)K / 192,
+                                    (long)(tail.second / WIDE_PART_BYTES) / left});
+          run(p);
+          break;
+        }
         case 19: run(GemmPlan{Gemm::wide, bm, bn, 1}); break;
         case 5: if (k64) ALR_GEMM(256, 256, 2, 2, 64, 1); else ALR_GEMM(256, 256, 2, 2, 32, 1); break;
         case 4: if (k64) ALR_GEMM(256, 256, 2, 4, 64, 1); else ALR_GEMM(256, 256, 2, 4, 32, 1); break;
@@ -1975,7 +2032,7 @@ alr_status alr_debug_gemm(int32_t dtype, const void* A, const void* W, float* C,
                           size_t scratch_bytes, alr_stream stream) {
   if (!A || !W || !C || M <= 0 || N <= 0 || K <= 0) return ALR_E_INVALID_ARG;
   if (N % 64 || K % 64) return ALR_E_UNSUPPORTED;
-  if (tile < 0 || (tile > 5 && tile < 17) || tile > 20) return ALR_E_INVALID_ARG;
+  if (tile < 0 || (tile > 5 && tile < 17) || tile > 21) return ALR_E_INVALID_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
   EpiLogits el;
   el.out = C;
@@ -1986,8 +2043,9 @@ alr_status alr_debug_gemm(int32_t dtype, const void* A, const void* W, float* C,
   alr_ctx dummy;
   if (dtype == ALR_BF16) {
     const bf16* Wk = (const bf16*)W;
-    if (tile == 18 || tile == 20) {  // split-K: partial sums in the scratch buffer
-      if (!splitk_scratch || scratch_bytes < (size_t)2 * M * N * 4) return ALR_E_WORKSPACE;
+    if (tile == 18 || tile == 20 || tile == 21) {  // partial sums in the scratch buffer
+      if (!splitk_scratch || (tile != 21 && scratch_bytes < (size_t)2 * M * N * 4))
+        return ALR_E_WORKSPACE;
       dummy.splitk_buf = static_cast<float*>(splitk_scratch);
       dummy.splitk_bytes = scratch_bytes;
     }

@@ -63,13 +63,15 @@ def test_gemm_few_rows(M, N, K):
     assert err <= 2e-5 * np.sqrt(K) * 4, err
 
 
-@pytest.mark.parametrize("tile", [17, 18, 19])
+@pytest.mark.parametrize("tile", [17, 18, 19, 21])
 @pytest.mark.parametrize("M,N,K", [(256, 256, 192), (255, 320, 256), (513, 192, 448),
-                                   (4400, 4160, 192), (2560, 7232, 256)])
+                                   (4400, 4160, 192), (2560, 7232, 256), (4400, 4160, 704),
+                                   (3900, 4352, 1152)])
 def test_gemm_wide(M, N, K, tile):
     """The hand-scheduled 256x256 kernel: three and four K steps (the least it takes), odd step
     counts, ragged rows and columns, and more tiles than CUs, so that workgroups go on to a
-    second tile whose copies run under the first one's epilogue; against float64."""
+    second tile whose copies run under the first one's epilogue; on 256 CUs the last two leave 50
+    and 16 tiles past the first round, which 21 cuts into 3 and 6 uneven slices; against float64."""
     _print(f"gemm wide tile {tile} {M}x{N}x{K}")
     g = torch.Generator().manual_seed(M + K)
     a, w = (torch.randn(s, generator=g).to(torch.bfloat16) for s in ((M, K), (N, K)))
