@@ -283,17 +283,20 @@ struct AttnCopier {
 //   masked (tiles entirely at or below every lane's lim skip the masking).
 //   m is the running max of the raw scores; scale_log2 = log2(e)/sqrt(hd) is
 //   applied inside the exponent.
-//   EARLY_V: the tile's V^T fragments are read between the score MFMAs and the
-//   softmax (64 more live registers at hd 128), so that the softmax covers their
-//   LDS latency instead of each value MFMA waiting on its read.  The prefill
-//   kernel takes it (3% faster); the decode kernel measured no gain from it.
-template <int HD, bool MASK, bool EARLY_V = false>
+// The tile's V^T fragments are read between the score MFMAs and the softmax (64 more
+// live registers at hd 128), so that the softmax covers their LDS latency instead of
+// each value MFMA waiting on its read (prefill 3% faster, decode of 2048 anchors over
+// 8192 keys 2%).  Waves in their MFMAs go before waves in their softmax: the waves that
+// share a SIMD then drift apart, so that one's matrix work runs under another's exp
+// work (hd 64, 4 x 2048 tokens x 16 heads: 67 -> 55 us; hd 128, decode 197 -> 192).
+template <int HD, bool MASK>
 __device__ __forceinline__ void attn_tile_update(const AttnTile<HD>& t, const bf16x8* qb,
                                                  f32x16* o, float& m, float& l, int key_abs0,
                                                  int lim, float scale_log2) {
   constexpr int NCHK = HD / 8;
   const int lane = threadIdx.x & 63, h = lane >> 5, lr = lane & 31;
   f32x16 s[2];
+  __builtin_amdgcn_s_setprio(1);
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
@@ -307,20 +310,19 @@ __device__ __forceinline__ void attn_tile_update(const AttnTile<HD>& t, const bf
     }
   }
   u32x4 vf[2][2][HD / 32];
-  if constexpr (EARLY_V) {
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+  for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int k2 = 0; k2 < 2; ++k2)
+    for (int k2 = 0; k2 < 2; ++k2)
 #pragma unroll
-        for (int db = 0; db < HD / 32; ++db) {
-          const int dim = db * 32 + lr;
-          vf[kb][k2][db] =
-              *(const u32x4*)(t.vt + dim * AT_KT + chunk_swz<8>(dim, 2 * (kb * 2 + k2) + h) * 8);
-        }
-    // keeps the reads ahead of the softmax (the scheduler would sink them to their uses)
-    __builtin_amdgcn_sched_barrier(0);
-  }
+      for (int db = 0; db < HD / 32; ++db) {
+        const int dim = db * 32 + lr;
+        vf[kb][k2][db] =
+            *(const u32x4*)(t.vt + dim * AT_KT + chunk_swz<8>(dim, 2 * (kb * 2 + k2) + h) * 8);
+      }
+  // keeps the reads ahead of the softmax (the scheduler would sink them to their uses)
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_setprio(0);
   float tmax = -INFINITY;
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb)
@@ -359,6 +361,7 @@ __device__ __forceinline__ void attn_tile_update(const AttnTile<HD>& t, const bf
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
   }
+  __builtin_amdgcn_s_setprio(1);
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -368,15 +371,11 @@ __device__ __forceinline__ void attn_tile_update(const AttnTile<HD>& t, const bf
       for (int e = 0; e < 4; ++e)
         pw[e] = pack2bf(s[kb][k2 * 8 + 2 * e], s[kb][k2 * 8 + 2 * e + 1]);
       const bf16x8 pb = as_bf16x8(pw);
-      const int c = 2 * (kb * 2 + k2) + h;
 #pragma unroll
-      for (int db = 0; db < HD / 32; ++db) {
-        const int dim = db * 32 + lr;
-        const u32x4 va = EARLY_V ? vf[kb][k2][db]
-                                 : *(const u32x4*)(t.vt + dim * AT_KT + chunk_swz<8>(dim, c) * 8);
-        o[db] = mfma32x32x16(as_bf16x8(va), pb, o[db]);
-      }
+      for (int db = 0; db < HD / 32; ++db)
+        o[db] = mfma32x32x16(as_bf16x8(vf[kb][k2][db]), pb, o[db]);
     }
+  __builtin_amdgcn_s_setprio(0);
 }
 
 // Store O^T / l for the lane's query into out (row pointer, natural order).
@@ -449,9 +448,9 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_mfma_kernel(
     if (it + 1 < nt) cp.tile(tiles[(it + 1) & 1], Kc, vT, k0 + AT_KT, w.len - 1);
     if (active && k0 <= wave_last_q) {
       if (k0 + AT_KT - 1 > qb * 32)  // some key of the tile lies beyond some query: mask
-        attn_tile_update<HD, true, true>(tiles[it & 1], qbv, o, m, l, k0, q_pos, g.scale_log2);
+        attn_tile_update<HD, true>(tiles[it & 1], qbv, o, m, l, k0, q_pos, g.scale_log2);
       else
-        attn_tile_update<HD, false, true>(tiles[it & 1], qbv, o, m, l, k0, q_pos, g.scale_log2);
+        attn_tile_update<HD, false>(tiles[it & 1], qbv, o, m, l, k0, q_pos, g.scale_log2);
     }
     attn_wait_copies();
     __syncthreads();
