@@ -1053,37 +1053,45 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__
 // fp32 products of few tiles.  A 64x64 tile of the kernel above is one long chain
 // of K steps, each waiting for its loads and two barriers, and products this small
 // give the chip only a handful of tiles, so the chain is all there is (M = 8, N =
-// 128, K = 512: 2 workgroups, 35 us).  Here a workgroup's WAVES waves share the K
-// of an 8 x 64 tile, 16 columns of K at a time straight from global memory into
-// registers (24 independent 16-byte loads per lane), and meet once in LDS: the
-// same product 13 us, the 8 x 384 x 128 one 11.8 -> 5.4 us.
-// Half-wave h of a wave holds rows 4 h .. 4 h + 3; lane l of it columns l and l + 32.
+// 128, K = 512: 2 workgroups, 35 us).  Here a workgroup's eight waves share the K
+// of 8 rows and PAIRS column pairs (c, c + 32), 16 columns of K at a time straight from
+// global memory into registers (all of a step's 16-byte loads in flight), and meet
+// once in LDS: 13 us for that product with PAIRS = 32.  PAIRS = 8 spreads the W rows
+// over four times the CUs, and four steps' loads fit the registers: 11 us; 8 x 384 x
+// 128 11.8 -> 4.4 us (5.3 with PAIRS = 32).
+// Lane l of a wave holds pair l % PAIRS of R rows.
 constexpr int GFS_M = 8;
 
-template <int TAG, int WAVES, class Epi>
-__global__ __launch_bounds__(64 * WAVES) void gemm_f32_small_kernel(
-    const float* __restrict__ A, int lda, const float* __restrict__ W, int ldw, int M, int N, int K,
-    Epi epi) {
-  __shared__ f32x2 red[WAVES][GFS_M][32];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, lc = lane & 31;
-  const int n0 = blockIdx.x * 64, m0 = blockIdx.y * GFS_M;
+template <int TAG, int PAIRS, class Epi>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void
+gemm_f32_small_kernel(const float* __restrict__ A, int lda, const float* __restrict__ W, int ldw,
+                      int M, int N, int K, Epi epi) {
+  constexpr int WAVES = 8;
+  constexpr int R = GFS_M * PAIRS / 64;
+  __shared__ f32x2 red[WAVES][GFS_M][PAIRS];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane / PAIRS, lc = lane % PAIRS;
+  const int n0 = (int)(blockIdx.x / (32 / PAIRS)) * 64 + (int)(blockIdx.x % (32 / PAIRS)) * PAIRS;
+  const int m0 = blockIdx.y * GFS_M;
   const float* w0 = W + (long)(n0 + lc) * ldw;  // N is a multiple of 64
   const float* w1 = w0 + (long)32 * ldw;
-  const float* a[4];
+  const float* a[R];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) a[i] = A + (long)min(m0 + 4 * h + i, M - 1) * lda;
-  f32x2 acc[4];
+  for (int i = 0; i < R; ++i) a[i] = A + (long)min(m0 + R * h + i, M - 1) * lda;
+  f32x2 acc[R];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) acc[i] = f32x2{0.f, 0.f};
-  for (int k0 = wave * 16; k0 < K; k0 += WAVES * 16) {  // K is a multiple of 16
-    f32x4 wl[4], wh[4], av[4][4];
+  for (int i = 0; i < R; ++i) acc[i] = f32x2{0.f, 0.f};
+  // a wave's columns are neighbours: its loads share cache lines (K is a multiple of 16)
+  const int k1 = K / 16 * (wave + 1) / WAVES * 16;
+#pragma unroll PAIRS == 8 ? 4 : 1
+  for (int k0 = K / 16 * wave / WAVES * 16; k0 < k1; k0 += 16) {
+    f32x4 wl[4], wh[4], av[R][4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       wl[j] = *(const f32x4*)(w0 + k0 + 4 * j);
       wh[j] = *(const f32x4*)(w1 + k0 + 4 * j);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < R; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) av[i][j] = *(const f32x4*)(a[i] + k0 + 4 * j);
 #pragma unroll
@@ -1091,16 +1099,16 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_f32_small_kernel(
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < R; ++i) {
           acc[i][0] = fmaf(av[i][j][e], wl[j][e], acc[i][0]);
           acc[i][1] = fmaf(av[i][j][e], wh[j][e], acc[i][1]);
         }
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) red[wave][4 * h + i][lc] = acc[i];
+  for (int i = 0; i < R; ++i) red[wave][R * h + i][lc] = acc[i];
   __syncthreads();
-  if (threadIdx.x >= GFS_M * 32) return;
-  const int r = threadIdx.x >> 5, c = threadIdx.x & 31;
+  if (threadIdx.x >= GFS_M * PAIRS) return;
+  const int r = threadIdx.x / PAIRS, c = threadIdx.x % PAIRS;
   f32x2 x = red[0][r][c];
 #pragma unroll
   for (int k = 1; k < WAVES; ++k) {

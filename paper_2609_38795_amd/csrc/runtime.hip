@@ -728,11 +728,18 @@ void launch_gemm(alr_ctx* ctx, const T* A, int lda, const T* W, int ldw, int M, 
     if (tm * tn >= ctx->n_cu) {
       gemm_f32_kernel<TAG, Epi><<<tm * tn, 256, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
     } else {
-      const dim3 grid(N / 64, (M + GFS_M - 1) / GFS_M);
-      if (K >= 256)
-        gemm_f32_small_kernel<TAG, 16, Epi><<<grid, 1024, 0, st>>>(A, lda, W, ldw, M, N, K, epi);
+      const int groups = N / 64, rows = (M + GFS_M - 1) / GFS_M;
+      auto small = [&](auto pairs) {
+        constexpr int P = decltype(pairs)::value;
+        gemm_f32_small_kernel<TAG, P, Epi>
+            <<<dim3(groups * (32 / P), rows), 512, 0, st>>>(A, lda, W, ldw, M, N, K, epi);
+      };
+      if constexpr (std::is_same<Epi, EpiLogits>::value)
+        small(std::integral_constant<int, 32>{});
+      else if (4 * groups * rows < ctx->n_cu)
+        small(std::integral_constant<int, 8>{});
       else
-        gemm_f32_small_kernel<TAG, 8, Epi><<<grid, 512, 0, st>>>(A, lda, W, ldw, M, N, K, epi);
+        small(std::integral_constant<int, 32>{});
     }
   }
 }
