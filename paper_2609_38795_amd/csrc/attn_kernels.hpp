@@ -187,7 +187,8 @@ constexpr int AT_KT = 64;
 // minimise the simulated makespan (list scheduling, largest item first, two
 // workgroups per CU, an item costing its tiles + AT_DECODE_ITEM_OVERHEAD)
 // among the ct that give at most AT_DECODE_MAX_ITEMS items and never fewer
-// than AT_DECODE_MIN_TILES tiles per item.
+// than AT_DECODE_MIN_TILES tiles per item (half of that where two tiles per CU
+// are more than there are).
 constexpr int AT_DECODE_MAX_ITEMS = 2048;
 constexpr int AT_DECODE_ITEM_OVERHEAD = 3;  // prologue, partial store and merge, in tiles
 constexpr int AT_DECODE_MIN_TILES = 4;

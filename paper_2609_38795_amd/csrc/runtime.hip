@@ -495,17 +495,20 @@ bool launch_splitk_resid_norm(alr_ctx* ctx, int S, int M, int N, const EpiResid&
 // A round of workgroups, one per CU, takes steps x (time of a K step of 64) plus
 // what a tile costs besides its K loop; slices add the fp32 partials they write
 // and re-read (4.2 TB/s) and a second launch, unless that is the reduce which
-// carries the following RMSNorm.  The constants are fits over M = 7 .. 8192, N =
-// 1024 .. 37888, K = 1024 .. 18944 (weights rotated through more than the last-level
-// cache).  A step of the 256x256 kernel takes longer the more CUs run it, as the
-// clock falls: 1.03 us on half of them, 1.35 us on all.  Where the lines lie:
-//   M <= 64 streams weights, so the 32- and 64-row tiles win; at M = 128 the 128-row
-//   ring tiles do (N = 28672, K = 4096: 52 us against 69 for 64x128 LDS-staged
-//   tiles and 85 for 256x256); from M = 256 on the 256x256 tiles, sliced so that
-//   they fill the CUs (M = 1024, N = 6144, K = 4096: 2 slices 48 us, 128x128 63;
-//   M = 2048: unsliced 83, 128x128 117).  128x128 LDS-staged tiles remain where
-//   256x256 ones would leave CUs idle and K is too short to slice (M = 8192,
-//   N = 1024, K = 1024: 23.6 against 25.7 us).
+// carries the following RMSNorm (3.4 us: M = 7, N = 1536, K = 1024 takes 6.4 us whole,
+// 4.0 + 3.1 sliced; M = 256 11.5 whole, 6.4 + 3.7 sliced).  The constants are fits over
+// M = 7 .. 8192, N = 1024 .. 37888, K = 1024 .. 18944 (weights rotated through more
+// than the last-level cache).  A step of the 256x256 kernel takes longer the more CUs
+// run it, as the clock falls: 1.03 us on half of them, 1.35 us on all.  Where the
+// lines lie:
+//   M <= 64 streams weights, so the 32- and 64-row tiles win, and up to 128 rows two
+//   64-row tiles do where 128-row ones leave CUs idle (M = 128, N = 8064, K = 4096: 26
+//   us against 36); else at M = 128 the 128-row ring tiles do (N = 28672, K = 4096:
+//   52 us against 69 for 64x128 LDS-staged tiles and 85 for 256x256); from M = 256 on
+//   the 256x256 tiles, sliced so that they fill the CUs (M = 1024, N = 6144, K = 4096:
+//   2 slices 48 us, 128x128 63; M = 2048: unsliced 83, 128x128 117).  128x128 LDS-staged
+//   tiles remain where 256x256 ones would leave CUs idle and K is too short to slice
+//   (M = 8192, N = 1024, K = 1024: 23.6 against 25.7 us).
 enum class Gemm { ring32, ring64, ring128x64, ring128, lds128, wide };
 struct GemmPlan {
   Gemm kernel;
@@ -532,7 +535,7 @@ GemmPlan pick_gemm(int M, int N, int K, int n_cu, size_t split_bytes, bool norm_
   float best_us = 0.f;
   for (const Kern& k : kerns) {
     // the smallest row tile that holds M, or tiles of 128 rows and more
-    if (k.bm == 32 ? M > 32 : (k.bm == 64 ? M <= 32 || M > 64 : M <= 64)) continue;
+    if (k.bm == 32 ? M > 32 : (k.bm == 64 ? M <= 32 || M > 128 : M <= 64)) continue;
     if (k.k == Gemm::lds128 && M <= FEW_ROWS) continue;  // the ring kernel of that tile is faster
     const long t = (long)((M + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn);
     for (int S = 1; S <= 8; S *= 2) {
@@ -545,7 +548,7 @@ GemmPlan pick_gemm(int M, int N, int K, int n_cu, size_t split_bytes, bool norm_
       const float step = k.k == Gemm::wide ? 0.7f + 0.65f * busy : k.step_us;
       float us = (float)rounds * ((float)(K / 64 / S) * step + k.tile_us +
                                   (k.k == Gemm::wide && S == 1 ? epi_us : 0.f));
-      if (S > 1) us += (float)S * M * N * (4.f / 4.2e6f) + (norm_follows ? 0.f : 3.f);
+      if (S > 1) us += (float)S * M * N * (4.f / 4.2e6f) + (norm_follows ? 0.f : 3.4f);
       int tail = 1;
       const long left = t % n_cu;
       if (k.k == Gemm::wide && S == 1 && t > n_cu && 2 * left <= n_cu && left > 0) {
@@ -724,7 +727,9 @@ void launch_gemm(alr_ctx* ctx, const T* A, int lda, const T* W, int ldw, int M, 
     }
   } else {
     const int tm = (M + GF_M - 1) / GF_M, tn = (N + GF_N - 1) / GF_N;
-    // 64x64 tiles pay where they fill the CUs (M = 1200, N = 1024, K = 128: 304 tiles)
+    // 64x64 tiles pay where they fill the CUs (M = 1200, N = 1024, K = 128: 304 tiles).
+    // Else 8 x 64 ones, or 8 x 16 where even those leave three CUs of four idle (the
+    // logits' statistics need whole 64-column groups).
     if (tm * tn >= ctx->n_cu) {
       gemm_f32_kernel<TAG, Epi><<<tm * tn, 256, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
     } else {
@@ -1606,8 +1611,13 @@ int plan_decode(const alr_config& c, int n_cu, int n, const int* seqs, const int
   }
   int max_nt = 1;
   for (const Grp& gr : gs) max_nt = std::max(max_nt, gr.ntile);
+  // A chunk more per row costs its merge about as much as two tiles fewer save
+  // where the items fill the CUs (256 anchors of the 1B-like model: 10.4 + 6.3 us at 4
+  // tiles and more, 9.9 + 7.2 at 2); where they leave most idle it is free (7 anchors
+  // of one 701-token sequence: 7.6 + 5.5 us and 5.6 + 5.6).
+  const int min_tiles = total_tiles <= 2L * n_cu ? AT_DECODE_MIN_TILES / 2 : AT_DECODE_MIN_TILES;
   const int ct_min = (int)std::max<long>(
-      AT_DECODE_MIN_TILES, (total_tiles + AT_DECODE_MAX_ITEMS - 1) / AT_DECODE_MAX_ITEMS);
+      min_tiles, (total_tiles + AT_DECODE_MAX_ITEMS - 1) / AT_DECODE_MAX_ITEMS);
   // logical item list for chunk length ct: (group index, chunk)
   auto list_items = [&](int ct, std::vector<std::pair<int, int>>& out, std::vector<int>& kvh) {
     out.clear();
