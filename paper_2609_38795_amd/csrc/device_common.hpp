@@ -152,13 +152,15 @@ __device__ __forceinline__ uint32_t lds_byte_addr(const void* p) {
 // One wave-wide 1 KB copy global -> LDS (global_load_lds_dwordx4): lane i
 // fetches 16 bytes at gbase + voff and writes them to LDS byte m0 + 16 i.  No
 // VGPR holds the data and no ds_write is issued.  The compiler does not see the
-// copy, so every wait on it is explicit.
+// copy, so every wait on it is explicit.  The s_nop is the one wait state that gfx9
+// asks for between a scalar write of m0 and an LDS copy that reads it; the compiler
+// inserts it for its own copies, but not inside an asm string.
 // m0 is named as clobbered for the reader; the compiler reserves it and uses
 // it in these kernels only for such copies (checked in their assembly).
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void copy_1k(uint32_t m0, uint32_t voff, const void* gbase) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :
                : "s"(m0), "v"(voff), "s"(gbase)
                : "memory", "m0");

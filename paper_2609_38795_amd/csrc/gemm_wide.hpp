@@ -37,11 +37,14 @@ namespace alr {
   "v_mfma_f32_16x16x32_bf16 " ALR_ACC(i, j) ", " ALR_FA(F, i) ", " ALR_FB(F, j) ", " ALR_ACC(i, j) "\n\t"
 #define ALR_MZ(F, i, j) \
   "v_mfma_f32_16x16x32_bf16 " ALR_ACC(i, j) ", " ALR_FA(F, i) ", " ALR_FB(F, j) ", 0\n\t"
-// LDS reads of block i (16 rows, 2 KB apart); copies of 32-row pieces of the A and W tiles
+// LDS reads of block i (16 rows, 2 KB apart); copies of 32-row pieces of the A and W
+// tiles.  M0 holds the LDS address of the copy, and one instruction has to stand between
+// its write and the copy that reads it: ALR_REFILL sets it two MFMAs before the first
+// copy, and each copy is followed by the write for the next (the last A copy's for W).
 #define ALR_RA(F, i) "ds_read_b128 " ALR_FA(F, i) ", v[112+" #F "] offset:2048*" #i "\n\t"
 #define ALR_RB(F, j) "ds_read_b128 " ALR_FB(F, j) ", v[114+" #F "] offset:2048*" #j "\n\t"
-#define ALR_CA(j) "s_add_u32 m0, %[lds], 4096*" #j "\n\tglobal_load_lds_dwordx4 v[96+" #j "], s[40:41]\n\t"
-#define ALR_CW(j) "s_add_u32 m0, %[lds], 32768+4096*" #j "\n\tglobal_load_lds_dwordx4 v[104+" #j "], s[42:43]\n\t"
+#define ALR_CA(j) "global_load_lds_dwordx4 v[96+" #j "], s[40:41]\n\ts_add_u32 m0, %[lds], 4096+4096*" #j "\n\t"
+#define ALR_CW(j) "global_load_lds_dwordx4 v[104+" #j "], s[42:43]\n\ts_add_u32 m0, %[lds], 36864+4096*" #j "\n\t"
 // One k half: 64 MFMAs in rows of eight (every other row backwards, so that
 // neighbours share an operand), with a slot for other work after every second.
 #define ALR_ROW_F(M, F, i, a, b, c, d) M(F, i, 0) M(F, i, 1) a M(F, i, 2) M(F, i, 3) b \
@@ -77,6 +80,7 @@ namespace alr {
 #define ALR_HALF0_(...) ALR_HALF0(__VA_ARGS__)
 #define ALR_HALF1_(...) ALR_HALF1(__VA_ARGS__)
 #define ALR_FREE "s_waitcnt lgkmcnt(0)\n\ts_barrier\n\t"
+#define ALR_REFILL ALR_FREE "s_mov_b32 m0, %[lds]\n\t"
 // the read addresses move to the other stage
 #define ALR_FLIP "v_xor_b32 v112, 0x10000, v112\n\tv_xor_b32 v113, 0x10000, v113\n\t" \
   "v_xor_b32 v114, 0x10000, v114\n\tv_xor_b32 v115, 0x10000, v115\n\t"
@@ -242,10 +246,10 @@ __global__ __launch_bounds__(256, 1) void gemm_bf16_wide_kernel(
         ALR_RA(0, 0) ALR_RB(0, 0) ALR_RB(0, 1) ALR_RB(0, 2) ALR_RB(0, 3) ALR_RB(0, 4) ALR_RB(0, 5) ALR_RB(0, 6)
         ALR_RB(0, 7) ALR_RA(0, 1) ALR_RA(0, 2) ALR_RA(0, 3) ALR_RA(0, 4) ALR_RA(0, 5) ALR_RA(0, 6) ALR_RA(0, 7)
         "s_waitcnt lgkmcnt(0)\n\t"
-        ALR_HALF0_(ALR_MZ, ALR_FREE, ALR_COPIES_A)
+        ALR_HALF0_(ALR_MZ, ALR_REFILL, ALR_COPIES_A)
         "s_branch 2f\n\t"
         "1:\n\t"
-        ALR_HALF0_(ALR_MF, ALR_FREE, ALR_COPIES_A)
+        ALR_HALF0_(ALR_MF, ALR_REFILL, ALR_COPIES_A)
         "2:\n\t"
         ALR_FLIP
         // the next step's copies have landed (the eight newest refill this one)
