@@ -79,6 +79,20 @@ typedef enum {
   ALR_PROF_COUNT = 14
 } alr_prof_site;
 
+/* Kernel that a bf16 product of the model takes at a launch site (host only, no GPU
+ * needed; the choice the compute calls make): `rows` rows at a GEMM site above, on a
+ * device of n_cu compute units, in a context of this config and these limits.  `cols`
+ * is the width of an output-head product that covers a panel of the vocabulary (corpus
+ * labels), a multiple of 64; 0, and at every other site, the site's own.  Writes the kernel to
+ * *kernel_out (0 = 32x64, 1 = 64x64, 2 = 128x64, 3 = 128x128 tiles of the few-row kernel, 4 =
+ * 128x128 LDS-staged, 5 = 256x256), its K slices, summed by a reduce, to *splits_out, and the K
+ * slices of the tiles past the last full round to *tail_out (1: not sliced).
+ * ALR_E_UNSUPPORTED for fp32, ALR_E_INVALID_ARG for a site without a GEMM or bad counts, the
+ * statuses of alr_check_config otherwise. */
+alr_status alr_debug_gemm_plan(const alr_config* cfg, const alr_limits* lim, int32_t n_cu,
+                               int32_t site, int32_t rows, int32_t cols, int32_t* kernel_out,
+                               int32_t* splits_out, int32_t* tail_out);
+
 /* Start timing every launch at `site` with HIP events recorded on the launch
  * stream, for up to `capacity` launches (later launches are not timed).
  * Creates 2*capacity events (host-side HIP objects, no device buffers). */

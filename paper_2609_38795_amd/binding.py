@@ -26,7 +26,7 @@ EXPORTS = ("alr_workspace_bytes", "alr_check_config", "alr_check_rollout", "alr_
            "alr_prefill", "alr_prefill_positions", "alr_rollout", "alr_rollout_topk",
            "alr_rollout_topk_noalloc",
            "alr_corpus_labels", "alr_ira_assemble", "alr_slot_weights", "alr_last_error", "alr_status_string", "alr_destroy",
-           "alr_debug_gemm", "alr_debug_decode_plan", "alr_profile_start", "alr_profile_stop",
+           "alr_debug_gemm", "alr_debug_decode_plan", "alr_debug_gemm_plan", "alr_profile_start", "alr_profile_stop",
            "alr_set_rollout_graphs")
 ALR_TOPK = 8
 
@@ -117,6 +117,8 @@ def load_library() -> ctypes.CDLL:
     lib.alr_debug_decode_plan.argtypes = [cfgp, i32, i32, i32p, i32, i32p, i32p, i32p, i32p, i32p,
                                           i32p, i32]
     lib.alr_debug_decode_plan.restype = ctypes.c_int
+    lib.alr_debug_gemm_plan.argtypes = [cfgp, limp, i32, i32, i32, i32, i32p, i32p, i32p]
+    lib.alr_debug_gemm_plan.restype = ctypes.c_int
     lib.alr_profile_start.argtypes = [vp, i32, i32]
     lib.alr_profile_start.restype = ctypes.c_int
     lib.alr_profile_stop.argtypes = [vp, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(i32)]
@@ -459,3 +461,15 @@ def debug_gemm(dtype: int, A, W, C, stream=None, tile: int = 0):
                             ctypes.c_void_p(s.cuda_stream))
     if st != 0:
         raise AlrError(st, "alr_debug_gemm")
+
+
+def gemm_plan(shape, limits: AlrLimits, site: str, rows: int, cols: int = 0, n_cu: int = 256):
+    """-> (kernel, K slices, K slices of the tiles past the last full round) of a bf16 product at a
+    launch site (alr_debug_gemm_plan; host only)."""
+    cfg = make_config(shape, 1)
+    out = [ctypes.c_int32() for _ in range(3)]
+    st = load_library().alr_debug_gemm_plan(ctypes.byref(cfg), ctypes.byref(limits), n_cu,
+                                            PROF_SITES[site], rows, cols, *(ctypes.byref(o) for o in out))
+    if st != 0:
+        raise AlrError(st, "alr_debug_gemm_plan")
+    return tuple(o.value for o in out)

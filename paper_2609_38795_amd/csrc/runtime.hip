@@ -616,16 +616,22 @@ void launch_plan(const GemmPlan& p, int n_cu, const bf16* A, int lda, const bf16
 }
 
 // Where a product may leave partial sums besides splitk_buf: the activation buffers
-// that hold nothing at its site.  Before the MLP that is the one for the gate's and up's
-// product, from there on (and at the output head) the query and attention rows.
-template <int TAG>
-std::pair<float*, size_t> tail_scratch(const alr_ctx* ctx) {
-  const Layout& L = ctx->L;
-  if (TAG == 0) return {ctx->splitk_buf, ctx->splitk_bytes};
-  if (TAG == ALR_PROF_PREFILL_QKV || TAG == ALR_PROF_DECODE_QKV || TAG == ALR_PROF_PREFILL_O ||
-      TAG == ALR_PROF_DECODE_O)
-    return {ctx->at<float>(L.act), L.i_tokpos - L.act};
-  return {ctx->at<float>(L.qbuf), L.act - L.qbuf};
+// that hold nothing at its site, as (offset, bytes) of the workspace.  Before the MLP that
+// is the one for the gate's and up's product, from there on (and at the output head) the
+// query and attention rows.
+std::pair<size_t, size_t> tail_scratch(const Layout& L, int site) {
+  if (site == ALR_PROF_PREFILL_QKV || site == ALR_PROF_DECODE_QKV || site == ALR_PROF_PREFILL_O ||
+      site == ALR_PROF_DECODE_O)
+    return {L.act, L.i_tokpos - L.act};
+  return {L.qbuf, L.act - L.qbuf};
+}
+
+// pick_gemm at a launch site.  All CUs reach their epilogues together, with nothing to
+// hide loads behind; SwiGLU's has none.
+GemmPlan site_plan(int site, int M, int N, int K, int n_cu, size_t split_bytes, bool norm_follows,
+                   size_t tail_bytes) {
+  const bool swiglu = site == ALR_PROF_PREFILL_GU || site == ALR_PROF_DECODE_GU;
+  return pick_gemm(M, N, K, n_cu, split_bytes, norm_follows, swiglu ? 0.f : 14.f, tail_bytes);
 }
 
 // norm_g / norm_out / normed: the RMSNorm that follows a residual update
@@ -643,7 +649,11 @@ void launch_gemm(alr_ctx* ctx, const T* A, int lda, const T* W, int ldw, int M, 
     bool epi_whole_k = false;
     if constexpr (std::is_same<Epi, EpiLogits>::value) epi_whole_k = epi.part != nullptr;
     const bool may_split = ctx->splitk_buf != nullptr && !epi_whole_k;
-    const std::pair<float*, size_t> tail = tail_scratch<TAG>(ctx);
+    std::pair<float*, size_t> tail{ctx->splitk_buf, ctx->splitk_bytes};  // the debug hook's
+    if constexpr (TAG != 0) {
+      const std::pair<size_t, size_t> t = tail_scratch(ctx->L, TAG);
+      tail = {ctx->at<float>(t.first), t.second};
+    }
     auto run = [&](const GemmPlan& p) {
       if (p.splits == 1) {
         launch_plan<TAG>(p, ctx->n_cu, A, lda, W, ldw, M, N, K, epi, st, tail.first);
@@ -661,9 +671,7 @@ void launch_gemm(alr_ctx* ctx, const T* A, int lda, const T* W, int ldw, int M, 
       launch_splitk_reduce(ctx->splitk_buf, (long)M * N, p.splits, M, N, epi, st);
     };
     if (force_tile == 0) {
-      // all CUs reach their epilogues together, with nothing to hide loads behind
-      const float epi_us = has_rows<Epi>::value && !std::is_same<Epi, EpiSwiGLU<bf16>>::value ? 14.f : 0.f;
-      run(pick_gemm(M, N, K, ctx->n_cu, may_split ? ctx->splitk_bytes : 0, norm_out != nullptr, epi_us,
+      run(site_plan(TAG, M, N, K, ctx->n_cu, may_split ? ctx->splitk_bytes : 0, norm_out != nullptr,
                     tail.second));
       return;
     }
@@ -2080,6 +2088,45 @@ static void prof_release(alr_ctx* ctx) {
   ctx->prof_ev.clear();
   ctx->prof_used = 0;
   ctx->prof_site = 0;
+}
+
+alr_status alr_debug_gemm_plan(const alr_config* cfg, const alr_limits* lim, int32_t n_cu,
+                               int32_t site, int32_t rows, int32_t cols, int32_t* kernel_out,
+                               int32_t* splits_out, int32_t* tail_out) {
+  if (!kernel_out || !splits_out || !tail_out || n_cu <= 0 || rows <= 0 || cols < 0 || cols % 64)
+    return ALR_E_INVALID_ARG;
+  alr_status st = alr_check_config(cfg, nullptr, 0);
+  if (st == ALR_OK) st = check_limits(lim, nullptr, 0);
+  if (st == ALR_OK) st = check_operand_sizes(*cfg, *lim, nullptr, 0);
+  if (st != ALR_OK) return st;
+  if (cfg->dtype != ALR_BF16) return ALR_E_UNSUPPORTED;
+  Layout L;
+  compute_layout(*cfg, *lim, L);
+  const int d = cfg->d_model, F = cfg->d_ffn, qd = cfg->n_heads * cfg->head_dim;
+  int N, K = d;
+  bool norm = false;
+  size_t split_bytes = L.splitk_bytes;
+  switch (site) {
+    case ALR_PROF_PREFILL_QKV:
+    case ALR_PROF_DECODE_QKV: N = qd + 2 * cfg->n_kv_heads * cfg->head_dim; break;
+    case ALR_PROF_PREFILL_O:
+    case ALR_PROF_DECODE_O: N = d; K = qd; norm = true; break;
+    case ALR_PROF_PREFILL_GU:
+    case ALR_PROF_DECODE_GU: N = 2 * F; break;
+    case ALR_PROF_PREFILL_DOWN:
+    case ALR_PROF_DECODE_DOWN: N = d; K = F; norm = true; break;
+    case ALR_PROF_LM_GEMM:
+      N = cols ? cols : cfg->vocab;
+      split_bytes = 0;  // the partials of the log-sum-exp need whole sums
+      break;
+    default: return ALR_E_INVALID_ARG;
+  }
+  const GemmPlan p = site_plan(site, rows, N, K, n_cu, split_bytes, norm,
+                               tail_scratch(L, site).second);
+  *kernel_out = (int32_t)p.kernel;
+  *splits_out = p.splits;
+  *tail_out = p.tail;
+  return ALR_OK;
 }
 
 alr_status alr_profile_start(alr_ctx* ctx, int32_t site, int32_t capacity) {

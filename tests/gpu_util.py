@@ -6,6 +6,12 @@ import numpy as np
 from paper_2609_38795_amd import binding, workloads as W
 
 
+def n_cu():
+    import torch
+
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
 def make_engine(inp, max_anchors=None, max_block=None):
     import torch
 

@@ -1,0 +1,49 @@
+"""Host-only checks of the kernel choice of the bf16 products (alr_debug_gemm_plan), which the GPU
+tests use to show that a case reaches the path it is there for."""
+import dataclasses
+
+import pytest
+
+from paper_2609_38795_amd import binding, workloads as W
+
+WIDE = 5
+
+
+def _plan(shape, site, rows, cols=0, tokens=8192, anchors=1024, n_cu=256):
+    return binding.gemm_plan(shape, binding.make_limits(tokens, 8, anchors, 16), site, rows, cols,
+                             n_cu)
+
+
+def test_headline_choices():
+    s = W.get("llama8b_like").shape
+    for site in ("prefill_qkv", "prefill_o", "prefill_gu", "prefill_down"):
+        assert _plan(s, site, 32768, tokens=32768) == (WIDE, 1, 1), site
+    assert _plan(s, "decode_qkv", 1024)[:2] == (WIDE, 2)
+    assert _plan(s, "decode_gu", 1024) == (WIDE, 1, 1)
+    assert _plan(s, "lm_gemm", 1024)[1:] == (1, 1)
+
+
+def test_slices_need_their_scratch():
+    """8 slices of few rows fit the split-K buffer; rows beyond what it was sized for are not cut."""
+    s = dataclasses.replace(W.get("small_bf16").shape, d_model=2048)
+    assert _plan(s, "decode_qkv", 8, anchors=8)[1] == 8
+    assert _plan(s, "prefill_qkv", 256, anchors=1)[1] == 1
+
+
+def test_sliced_last_round_depends_on_the_device():
+    """7B-like down projection of 10,900 rows: 602 tiles leave 90 of a third round on 256 CUs, and none
+    on 301."""
+    s = W.get("vl_prefix_7b").shape
+    assert _plan(s, "prefill_down", 10900, tokens=10900) == (WIDE, 1, 2)
+    assert _plan(s, "prefill_down", 10900, tokens=10900, n_cu=301) == (WIDE, 1, 1)
+
+
+def test_plan_errors():
+    s = W.get("small_bf16").shape
+    for bad in (dict(site="prefill_attn"), dict(rows=0), dict(cols=32), dict(n_cu=0)):
+        with pytest.raises(binding.AlrError) as e:
+            _plan(s, **{"site": "decode_o", "rows": 4, **bad})
+        assert e.value.status == 1, bad
+    with pytest.raises(binding.AlrError) as e:
+        _plan(W.get("tiny_fp32").shape, "decode_o", 4)
+    assert e.value.status == 5

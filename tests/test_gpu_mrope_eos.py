@@ -5,7 +5,7 @@ import pytest
 from oracle import labels as LB
 from paper_2609_38795_amd import binding, workloads as W
 from parity import compare
-from gpu_util import make_engine
+from gpu_util import make_engine, n_cu
 
 pytestmark = pytest.mark.gpu
 
@@ -53,15 +53,19 @@ def _prefill(eng, inp, pos):
 
 
 # the last case puts section boundaries (6 and 19) inside runs of four rotary dims and is wide
-# enough (d_model 512) for the rollout's QKV product to be split over K, so the split-K reduce's
-# four-column RoPE meets both a shared axis and the per-dim fallback
+# enough (d_model 2048) for the rollout's QKV product to be split over K in 8 slices, so the split-K
+# reduce's four-column RoPE meets runs whose dims follow different axes
 @pytest.mark.parametrize("dtype,hd,H,G,sections,d_model", [("f32", 32, 4, 2, (4, 6, 6), 256),
                                                            ("bf16", 128, 4, 2, (16, 24, 24), 256),
                                                            ("bf16", 64, 8, 2, (8, 12, 12), 256),
-                                                           ("bf16", 64, 8, 2, (6, 13, 13), 512)])
+                                                           ("bf16", 64, 8, 2, (6, 13, 13), 2048)])
 def test_mrope_rollout_matches_oracle(dtype, hd, H, G, sections, d_model):
     inp, pos = _mrope_inputs(dtype, hd, H, G, sections, side=6, seed=hd + H, d_model=d_model)
     w = inp.workload
+    if d_model == 2048:
+        lim = binding.make_limits(w.n_tokens, w.n_seq, w.n_anchors, w.block)
+        _, splits, _ = binding.gemm_plan(w.shape, lim, "decode_qkv", w.n_anchors, n_cu=n_cu())
+        assert splits == 8
     eng = make_engine(inp)
     _prefill(eng, inp, pos)
     sel = np.arange(len(inp.anchor_seq))
