@@ -118,14 +118,26 @@ def test_rollout_batches_agree():
 
 
 # ------------------------------------------------------------------ fp32 workload
-def _full_compare(inp, sel=None, block=None):
+def _full_compare(inp, sel=None, block=None, whole_batch=False):
+    """Rolls out the anchors `sel` (whole_batch: every anchor) and compares those of `sel`."""
     w = inp.workload
     block = block or w.block
-    sel = np.arange(w.n_anchors) if sel is None else np.asarray(sel)
-    eng = make_engine(inp, max_anchors=len(sel), max_block=block)
+    n = len(inp.anchor_seq)
+    sel = np.arange(n) if sel is None else np.asarray(sel)
+    batch = np.arange(n) if whole_batch else sel
+    eng = make_engine(inp, max_anchors=len(batch), max_block=block)
     prefill(eng, inp)
-    rep = compare(inp, w.shape, sel, runner(eng, inp.anchor_seq[sel], inp.anchor_pos[sel], block),
-                  block)
+    run = runner(eng, inp.anchor_seq[batch], inp.anchor_pos[batch], block)
+
+    def gpu_run(forced):
+        if forced is not None and whole_batch:  # the other anchors stay greedy
+            every = np.full((n, block), -1, np.int64)
+            every[sel] = forced
+            forced = every
+        out = run(forced)
+        return tuple(x[sel] for x in out) if whole_batch else out
+
+    rep = compare(inp, w.shape, sel, gpu_run, block)
     eng.close()
     _print(rep)
     return rep
@@ -211,7 +223,7 @@ def test_wide_residual_rows(dtype):
     inp = W.Inputs(w, W.random_weights(w.shape, 8448, scale=0.02, norm_gain="random"),
                    W.random_tokens(512, (2, 96), 29, dist="zipf"),
                    *W.random_anchors(2, 96, 33, 0, 95, 12), None, None)
-    rep = _full_compare(inp, sel=np.array([0, 16, 32, 33, 50, 65]))
+    rep = _full_compare(inp, sel=np.array([0, 16, 32, 33, 50, 65]), whole_batch=True)
     assert rep.ok()
 
 
