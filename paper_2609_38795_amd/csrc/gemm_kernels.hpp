@@ -94,12 +94,13 @@ struct EpiQKV {
   }
   // Columns c..c+3 and c+32..c+35 of one row (c a multiple of 4 in the low
   // half of a 64-column group), for the split-K reduce: the same arithmetic
-  // per element as operator(), with 16-byte loads of the RoPE factors (the
-  // four dims share a head) and 8-byte bf16 stores.
+  // per element as operator(), with 16-byte loads of the RoPE factors and 8-byte
+  // bf16 stores where the four dims share a head (half a multiple of 4: a run starts
+  // at a multiple of 4 of the list), else one by one (as head size 36).
   __device__ __forceinline__ void quad(int row, int c, const f32x4& lo, const f32x4& hi) const {
     const int half = hd >> 1;
     const int qd = H * hd, kd = G * hd;
-    if (c < qd + kd) {
+    if (c < qd + kd && (half & 3) == 0) {
       OutT* dst;
       int cl;
       if (c < qd) {
@@ -122,7 +123,7 @@ struct EpiQKV {
       }
       st4(dst + head * hd + i, a);
       st4(dst + head * hd + i + half, b);
-    } else if (vt_col) {
+    } else if (c < qd + kd || vt_col) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) (*this)(row, c + e, lo[e], hi[e]);
     } else {
@@ -165,7 +166,12 @@ struct EpiQKV {
     int r[NR];
 #pragma unroll
     for (int t = 0; t < NR; ++t) r[t] = rb + QS * (t >> 2) + (t & 3);
-    if (c < qd + kd) {
+    if (c < qd + kd && (half & 1)) {
+      // the two columns of a lane pair may lie in different heads (head size 50)
+#pragma unroll
+      for (int t = 0; t < NR; ++t)
+        if (r[t] < M) (*this)(r[t], c, lo[t], hi[t]);
+    } else if (c < qd + kd) {
       OutT* base;
       long rs;
       int cl;
@@ -183,8 +189,8 @@ struct EpiQKV {
       f32x2 w[NR];
 #pragma unroll
       for (int t = 0; t < NR; ++t) w[t] = rope[(long)min(r[t], M - 1) * half + i];
-      // The two lanes of a column pair (i even, i+1 in the same head since half
-      // is even) trade one value of each half per two rows, so the even lane
+      // The two lanes of a column pair (i even, i+1 in the same head, half being
+      // even here) trade one value of each half per two rows, so the even lane
       // writes row r at i, i+1 and the odd lane row r+1: one store of two
       // elements per half instead of two single-element stores.
       const int odd = c & 1;
