@@ -1213,14 +1213,19 @@ alr_status upload(alr_ctx* ctx, void* dst, const void* src, size_t bytes, hipStr
 // slots.  At 2 x 96 anchors x 16 slots of 2 x 1024 tokens (d 3584, vocab 152064)
 // that is 1,206 rows in 7 products instead of 16 products of 192 rows that each
 // read the whole 1.09 GB head (9.5 -> 1.7 ms per call).  Full log-prob rows go slot by slot, where the
-// product writes the caller's rows itself.
+// product writes the caller's rows itself.  So does a call that is captured: a replay takes
+// the anchors from the tables as they are then, and a list of positions made for others
+// would send the expansion to rows that were never labelled.
 template <typename T>
 alr_status corpus_impl(alr_ctx* ctx, int n, int block, const LabelDst& out, float* corpus_logp,
                        float* gate_soft, float* gate_hard, hipStream_t st) {
   const alr_config& c = ctx->cfg;
   const Layout& L = ctx->L;
   const int d = c.d_model, V = c.vocab;
-  if (!out.logprobs) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  ALR_HIP(ctx, hipStreamIsCapturing(st, &cap));
+  const bool by_slot = out.logprobs != nullptr || cap != hipStreamCaptureStatusNone;
+  if (!by_slot) {
     const int D = (int)ctx->h_urow.size();
     const int* urow = ctx->at<int>(L.i_urow);
     LabelState* state = ctx->at<LabelState>(L.label_state);
@@ -1255,7 +1260,7 @@ alr_status corpus_impl(alr_ctx* ctx, int n, int block, const LabelDst& out, floa
         out.top_logp, out.tail, corpus_logp);
     ALR_LAUNCHED(ctx, "corpus label expansion");
   }
-  for (int s = 0; out.logprobs && s < block; ++s) {
+  for (int s = 0; by_slot && s < block; ++s) {
     corpus_rows_kernel<T><<<n, 256, 0, st>>>(
         ctx->at<T>(L.xnorm), ctx->at<T>(L.hf_store), ctx->at<int>(L.i_atok),
         ctx->at<int>(L.i_apos), ctx->at<int>(L.i_alen), ctx->at<int>(L.i_ctok), s, d,

@@ -8,7 +8,7 @@ synchronisations) and is compared with the same call made with graphs off.
 import numpy as np
 import pytest
 
-from paper_2609_38795_amd import workloads as W
+from paper_2609_38795_amd import binding, workloads as W
 from gpu_util import make_engine, prefill
 
 pytestmark = pytest.mark.gpu
@@ -140,4 +140,49 @@ def test_rollout_graph_cache_eviction():
     # switching graphs off drops the cache; plain launches still match
     eng.set_rollout_graphs(False)
     _same(_host(eng.rollout(inp.anchor_seq, inp.anchor_pos, w.block, out=outs[0])), ref, "graphs off")
+    eng.close()
+
+
+@pytest.mark.parametrize("dtype,hd", [("bf16", 128), ("f32", 32)])
+def test_corpus_labels_captured_by_the_caller(dtype, hd):
+    """Top-8 corpus labels recorded into a graph of the caller's: each replay against the eager call,
+    with a prefill and torch arithmetic between replays.  The tables are read when the graph runs, so
+    a replay after a call with other anchors labels those, none of which it was recorded for."""
+    inp = _workload(dtype, hd)
+    w = inp.workload
+    n = len(inp.anchor_seq)
+    a_seq, a_pos = inp.anchor_seq, inp.anchor_pos
+    b_seq, b_pos = a_seq[::-1].copy(), ((a_pos[::-1] + 150) % w.seq_len).astype(np.int32)
+    st = torch.cuda.Stream()
+    eng = binding.Engine(w.shape, inp.weights, w.max_pos,
+                         binding.make_limits(w.n_tokens, w.n_seq, n, w.block),
+                         device=torch.device("cuda:0"), stream=st)
+    prefill(eng, inp)
+    torch.cuda.synchronize()
+    keys = ("argmax", "top_ids", "gate_hard", "top_logp", "tail", "corpus_logp", "gate_soft")
+    refs = [dict(zip(keys, _host([eng.corpus_labels(s, p, w.block)[k] for k in keys])))
+            for s, p in ((b_seq, b_pos), (a_seq, a_pos))]
+    assert not np.array_equal(refs[0]["argmax"], refs[1]["argmax"])
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st):
+        out = eng.corpus_labels(a_seq, a_pos, w.block)
+
+    def replay(ref, what):
+        with torch.cuda.stream(st):
+            g.replay()
+        got = dict(zip(keys, _host([out[k] for k in keys])))
+        for k in keys[:3]:
+            assert np.array_equal(got[k], ref[k]), f"{what}: {k}"
+        for k in keys[3:]:  # the graph labels slot by slot: other sums of the same 32-bit values
+            np.testing.assert_allclose(got[k], ref[k], rtol=4e-6, atol=4e-6, err_msg=f"{what}: {k}")
+
+    for i in range(3):
+        _print(f"  replay {i}")
+        replay(refs[1], f"replay {i}")
+        prefill(eng, inp)
+        _ = (out["tail"] * 2.0).sum().item()
+        torch.cuda.synchronize()
+    _host(eng.rollout(b_seq, b_pos, w.block))
+    _print("  replay after a rollout of other anchors")
+    replay(refs[0], "other anchors")
     eng.close()
