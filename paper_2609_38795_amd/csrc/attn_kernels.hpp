@@ -52,7 +52,12 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(
   __shared__ float ms[4], ls[4];
   __shared__ float os[4][256];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int row = (int)(blockIdx.x / g.H), head = (int)(blockIdx.x % g.H);
+  int row = (int)(blockIdx.x / g.H);
+  const int head = (int)(blockIdx.x % g.H);
+  if (blockIdx.y > 0) {
+    row += (int)(blockIdx.y * (gridDim.x / g.H));
+    if (row >= n_rows) return;  // uniform over the workgroup
+  }
   const int kvh = head / (g.H / g.G);
   const int hd = g.hd;
   const long kv_rs = (long)g.G * hd;

@@ -766,13 +766,16 @@ AttnGeom geom(const alr_config& c) {
   return g;
 }
 
-// Whole 16-byte loads of key and value rows where every row starts on one.
+// Whole 16-byte loads of key and value rows where every row starts on one.  A grid
+// dimension holds fewer than 2^32 threads (a launch beyond wraps without an error), so
+// rows past about 2^22 (row, head) pairs go along y.
 template <typename T>
 void launch_attn_generic(const T* q, const T* kc, const T* vc, const T* kp, const T* vp,
                          long priv_rs, int n_priv, const int* row_start, const int* apos, T* out,
                          int rows, const AttnGeom& g, hipStream_t st) {
   constexpr int VEC = 16 / (int)sizeof(T);
-  const unsigned grid = (unsigned)((long)rows * g.H);
+  const int per_y = std::min(rows, std::max(1, (1 << 22) / g.H));
+  const dim3 grid((unsigned)(per_y * g.H), (unsigned)((rows + per_y - 1) / per_y));
   if (g.hd % VEC == 0)
     attn_generic_kernel<T, VEC><<<grid, 256, 0, st>>>(q, kc, vc, kp, vp, priv_rs, n_priv,
                                                       row_start, apos, out, rows, g);

@@ -206,6 +206,27 @@ def test_generic_attention_head_sizes(dtype, hd, H, G):
     assert rep.ok()
 
 
+def test_generic_attention_past_one_grid_dimension():
+    """More (query, head) pairs than one grid dimension holds workgroups of 256 threads (2^24): the
+    last sequences repeat the first ones' tokens, so their rows are bit-identical to rows of the first
+    2^24 pairs, which the other tests of this kernel cover."""
+    base = W.get("tiny_fp32")
+    n_seq, length, H = 8080, 65, 32
+    w = W.scaled(base, "grid", n_layers=1, d_model=64, n_heads=H, n_kv_heads=H, head_dim=2,
+                 d_ffn=64, vocab=64, feat_layers=(0,), n_seq=n_seq, seq_len=length, block=1)
+    assert w.n_tokens * H > 1 << 24
+    tok = W.random_tokens(64, (n_seq, length), 3)
+    tok[-40:] = tok[:40]
+    inp = W.Inputs(w, W.random_weights(w.shape, 4, scale=0.3, norm_gain="random"), tok,
+                   np.zeros(1, np.int32), np.zeros(1, np.int32), None, None)
+    eng = make_engine(inp, max_anchors=1)
+    fo = prefill(eng, inp, feats=True).view(n_seq, length, -1)
+    torch.cuda.synchronize()
+    same = torch.equal(fo[-40:], fo[:40])
+    assert same
+    eng.close()
+
+
 @pytest.mark.parametrize("hd,H,G,tokens,kernel", [(36, 32, 16, 90, 2), (100, 16, 16, 90, 2),
                                                   (10, 64, 32, 90, 2), (50, 32, 32, 90, 2),
                                                   (50, 32, 32, 400, 4), (50, 32, 32, 1000, 5)])
