@@ -107,8 +107,10 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(
     }
     const float sc = (j < n_total) ? dot * g.scale_log2 : -INFINITY;
     const float m_new = fmaxf(m, wave_max(sc));
-    const float alpha = fast_exp2(m - m_new);
-    const float p = (j < n_total) ? fast_exp2(sc - m_new) : 0.f;
+    // while a wave has met only scores of -inf, weights are taken against 0
+    const float ref = (m_new == -INFINITY) ? 0.f : m_new;
+    const float alpha = fast_exp2(m - ref);
+    const float p = (j < n_total) ? fast_exp2(sc - ref) : 0.f;
     l = l * alpha + wave_sum(p);
     ps[wave][lane] = p;  // read back by this wave alone
 #pragma unroll

@@ -227,6 +227,35 @@ def test_generic_attention_past_one_grid_dimension():
     eng.close()
 
 
+def test_generic_attention_tile_of_minus_infinity():
+    """A query whose scores against all keys of one wave's tile overflow to -inf (weight 0): keys
+    64..127 hold token 1, its key is -1e19 times the query of token 2 along one rotary dim that
+    hardly turns; token 0 has a zero key.  The row of token 2 is the mean of the other values."""
+    base = W.get("tiny_fp32")
+    w = W.scaled(base, "minus_inf", n_layers=1, d_model=64, n_heads=1, n_kv_heads=1, head_dim=64,
+                 d_ffn=64, vocab=64, feat_layers=(0,), rope_base=1e9, n_seq=1, seq_len=129, block=1)
+    wts = W.random_weights(w.shape, 6, scale=0.3)
+    wts["tok_embed"][:] = 0
+    for t in range(3):
+        wts["tok_embed"][t, t] = 1
+    ly = wts["layers"][0]
+    for k in ("wq", "wk", "w_down"):
+        ly[k][:] = 0
+    ly["wk"][31, 1], ly["wq"][31, 2] = -1e19, 1e20
+    tok = np.zeros((1, 129), np.int64)
+    tok[0, 64:128], tok[0, 128] = 1, 2
+    inp = W.Inputs(w, wts, tok, np.zeros(1, np.int32), np.zeros(1, np.int32), None, None)
+    eng = make_engine(inp, max_anchors=1)
+    row = prefill(eng, inp, feats=True)[128, 0].double().cpu().numpy()
+    eng.close()
+    f64 = {k: np.asarray(ly[k], np.float64) for k in ("wv", "wo", "attn_norm")}
+    e = np.asarray(wts["tok_embed"], np.float64)[:3]
+    v = (e / np.sqrt((e * e).mean(1, keepdims=True) + w.shape.rms_eps) * f64["attn_norm"]) @ f64["wv"].T
+    want = e[2] + f64["wo"] @ ((64 * v[0] + v[2]) / 65)
+    # 65 equal weights and 64 products per output, in 32 bits
+    np.testing.assert_allclose(row, want, rtol=0, atol=1e-5 * np.abs(want).max())
+
+
 @pytest.mark.parametrize("hd,H,G,tokens,kernel", [(36, 32, 16, 90, 2), (100, 16, 16, 90, 2),
                                                   (10, 64, 32, 90, 2), (50, 32, 32, 90, 2),
                                                   (50, 32, 32, 400, 4), (50, 32, 32, 1000, 5)])
