@@ -420,7 +420,8 @@ __device__ __forceinline__ void block_pop8(float (&tv)[L], int (&ti)[L], Top8& o
 // the rows with an insertion list per thread took 248 us at 192 rows of 152064 (29 M
 // logits); a panel of 1206 rows x 24064 columns, as many logits, takes 33 us.  What
 // bounds it is the chain of 16 block-wide picks.  The sum adds the other groups' partial sums and the unselected
-// entries of these, so nothing cancels.  Ids and column 0 are relative to z.
+// entries of these, so nothing cancels.  Ids and column 0 are relative to z.  NaN
+// logits are passed over (the row's sum of exponentials, and so its log-probs, are NaN).
 __device__ __forceinline__ float row_top8(const LogitPart* pr, int n, const float* z, float m,
                                           Top8Scratch& sc) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -433,7 +434,7 @@ __device__ __forceinline__ float row_top8(const LogitPart* pr, int n, const floa
       ti[j] = 0x7FFFFFFF;
     }
     for (int g = threadIdx.x; g < n; g += 256) {
-      const float gm = pr[g].m;
+      const float pm = pr[g].m, gm = pm == pm ? pm : -INFINITY;  // NaN: a group of NaN logits
       // groups rise within a thread: an equal max ranks after the ones held
       if (gm > tv[ALR_K_TOP - 1] || ti[ALR_K_TOP - 1] == 0x7FFFFFFF) {
         float pv = gm;
@@ -473,9 +474,10 @@ __device__ __forceinline__ float row_top8(const LogitPart* pr, int n, const floa
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const int g = sc.groups.i[wave + 4 * h];
-    const bool have = g < n;
+    const float v = g < n ? z[g * 64 + lane] : -INFINITY;
+    const bool have = g < n && v == v;
     ei[h] = have ? g * 64 + lane : 0x7FFFFFFF;
-    ev[h] = have ? z[ei[h]] : -INFINITY;
+    ev[h] = have ? v : -INFINITY;
   }
   if (ranks_before(ev[1], ei[1], ev[0], ei[0])) {
     const float v = ev[0];

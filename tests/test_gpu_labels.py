@@ -247,3 +247,47 @@ def test_corpus_labels_panels_match_rows(dtype, vocab, block, max_anchors):
     tail = np.where(mask_top, np.exp(lpn[ok].astype(np.float64)), 0).sum(-1)
     np.testing.assert_allclose(_np(a["tail"]).reshape(-1)[ok], tail, rtol=1e-5, atol=1e-7)
     eng.close()
+
+
+@pytest.mark.parametrize("name", ["tiny_fp32", "small_bf16"])
+def test_top8_passes_nan_logits_over(name):
+    """NaN rows of the output head (two of them, and a whole 64-column group): log-probs and tail
+    become NaN, but the tokens and the top 8 are the best of the other columns, as in the greedy rollout
+    and in the per-slot labels."""
+    base = W.get(name)
+    w = W.scaled(base, f"nan_{name}", n_layers=2, feat_layers=(0, 1), vocab=512, n_seq=1,
+                 seq_len=100, anchors_per_seq=6, anchor_lo=0, anchor_hi=99, block=3)
+    wts = W.random_weights(w.shape, 9, scale=0.1)
+    a_seq, a_pos = W.random_anchors(1, 100, 6, 0, 99, 2)
+    inp = W.Inputs(w, wts, W.random_tokens(512, (1, 100), 5), a_seq, a_pos, None, None)
+    forced = torch.from_numpy(W.random_tokens(512, (6, 3), 7)).to(torch.int32).cuda()
+    eng = make_engine(inp)
+    prefill(eng, inp)
+    _, lp, _ = eng.rollout(a_seq, a_pos, 3, forced=forced)
+    cl = eng.corpus_labels(a_seq, a_pos, 3, want_logprobs=True)
+    lp, clp = lp.clone(), cl["logprobs"].clone()
+    valid = cl["argmax"] >= 0
+    bad = torch.zeros(512, dtype=torch.bool, device="cuda")
+    bad[128:192] = True
+    bad[lp[0, 0].argmax()] = True  # the best column of one row
+    bad[lp[3, 1].argmax()] = True
+    rows = bad.nonzero().flatten().cpu().numpy()
+    wts["lm_head"][rows] = np.nan if w.shape.dtype == "f32" else 0x7FC0
+    eng.close()
+    eng = make_engine(inp)
+    prefill(eng, inp)
+
+    def best(z):
+        z = z.masked_fill(bad, -torch.inf).cpu().numpy()
+        return np.argsort(-z, axis=-1, kind="stable")[..., :8]
+
+    tok, ids, tl, tt, _, _ = eng.rollout_topk(a_seq, a_pos, 3, forced=forced)
+    greedy, _, _ = eng.rollout(a_seq, a_pos, 3, forced=forced)
+    assert np.array_equal(_np(ids), best(lp))
+    assert np.array_equal(_np(tok), best(lp)[..., 0]) and np.array_equal(_np(greedy), _np(tok))
+    assert torch.isnan(tl).all() and torch.isnan(tt).all()
+    for form in (False, True):
+        c = eng.corpus_labels(a_seq, a_pos, 3, want_logprobs=form)
+        assert np.array_equal(_np(c["top_ids"][valid]), best(clp[valid])), form
+        assert torch.isnan(c["top_logp"][valid]).all() and torch.isnan(c["tail"][valid]).all(), form
+    eng.close()
