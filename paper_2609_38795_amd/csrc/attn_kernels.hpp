@@ -20,16 +20,17 @@ struct AttnGeom {
 };
 
 // ------------------------------------------------------------------ generic kernel
-// One workgroup per (query row, head), its four waves taking 64-key tiles in
-// turn and merging their softmax states at the end.  Scores: a lane per key.
-// Weighted sum: lanes over VEC dimensions each, the wave's remaining lanes over
-// keys.  Handles any even hd <= 256 (VEC = 2; whole 16-byte loads where hd is a
-// multiple of their elements).  Used for the fp32 path and for head sizes the
+// WPI waves per item, an item being a (query row, head): a workgroup of four waves that
+// take 64-key tiles in turn and merge their softmax states at the end, or a wave each.
+// Scores: a lane per key.  Weighted sum: lanes over VEC dimensions each, the wave's
+// remaining lanes over keys.  Handles any even hd <= 256 (VEC = 2; whole 16-byte loads
+// where hd is a multiple of their elements).  Used for the fp32 path and for head sizes the
 // MFMA kernels do not cover.
-// What bounds it at the sizes it is used for (8 .. 600 rows of a few hundred keys)
-// is the chain of memory round trips: one wave over all keys of a row, one
-// key after the other, took 32 us at 128 rows x 4 heads, hd 32; a tile's key and
-// value rows are now all loaded before the first score (5.8 us).
+// What bounds it with few rows (8 .. 600 of a few hundred keys) is the chain of memory
+// round trips: one wave over all keys of a row, one key after the other, took 32 us at
+// 128 rows x 4 heads, hd 32; a tile's key and value rows are now all loaded before the
+// first score, and the four waves share the keys (5.8 us).  With many rows it is the
+// instructions per row, and a wave per row is faster (generic_shares_keys).
 //   prefill (priv == nullptr): row r is corpus token r, sequence start
 //     row_start[r]; it sees shared rows row_start[r] .. r.
 //   decode: row r is sorted anchor r with shared rows tok0[r] .. tok0[r] +
@@ -39,31 +40,36 @@ struct alignas(sizeof(T) * N) EltVec {
   T v[N];
 };
 
-template <typename T, int VEC>
+template <typename T, int VEC, int WPI>
 __global__ __launch_bounds__(256) void attn_generic_kernel(
     const T* __restrict__ Q, const T* __restrict__ Kc, const T* __restrict__ Vc,
     const T* __restrict__ Kp, const T* __restrict__ Vp, long priv_rs, int n_priv,
     const int* __restrict__ row_start, const int* __restrict__ apos, T* __restrict__ O,
-    int n_rows, AttnGeom g) {
+    int n_rows, int rows_y, AttnGeom g) {
   using V = EltVec<T, VEC>;
   constexpr int NC = (256 / VEC + 63) / 64;  // VEC-runs of dimensions per lane
-  __shared__ float qs[256];
+  constexpr int IPB = 4 / WPI;               // items per workgroup
+  constexpr int PF = WPI == 4 ? 8 : 4;     // passes of value rows loaded ahead
+  __shared__ float qs[IPB][256];
   __shared__ float ps[4][64];
-  __shared__ float ms[4], ls[4];
-  __shared__ float os[4][256];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int row = (int)(blockIdx.x / g.H);
-  const int head = (int)(blockIdx.x % g.H);
-  if (blockIdx.y > 0) {
-    row += (int)(blockIdx.y * (gridDim.x / g.H));
-    if (row >= n_rows) return;  // uniform over the workgroup
-  }
-  const int kvh = head / (g.H / g.G);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int slot = WPI == 4 ? 0 : wave;
   const int hd = g.hd;
+  const unsigned item = blockIdx.x * IPB + slot;
+  int row = (int)(item / (unsigned)g.H);
+  const int head = (int)item - row * g.H;
+  bool valid = row < rows_y;
+  row += (int)blockIdx.y * rows_y;
+  valid = valid && row < n_rows;
+  if (WPI == 4 && !valid) return;  // uniform over the workgroup
+  if (!valid) row = 0;
+  const int kvh = head / (g.H / g.G);
   const long kv_rs = (long)g.G * hd;
-  if ((int)threadIdx.x < hd)
-    qs[threadIdx.x] = Elt<T>::ld(Q + ((long)row * g.H + head) * hd + threadIdx.x);
+  for (int d = (int)threadIdx.x % (64 * WPI); d < hd; d += 64 * WPI)
+    qs[slot][d] = Elt<T>::ld(Q + ((long)row * g.H + head) * hd + d);
   __syncthreads();
+  if (!valid) return;  // the last barrier where an item is one wave's
   const int first = row_start[row];
   const int n_shared = (Kp == nullptr) ? row - first + 1 : apos[row] + 1;
   const int n_total = (Kp == nullptr) ? n_shared : n_shared + n_priv;
@@ -86,24 +92,24 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(
   for (int i = 0; i < NC; ++i)
 #pragma unroll
     for (int e = 0; e < VEC; ++e) acc[i][e] = 0.f;
-  for (int j0 = wave * 64; j0 < n_total; j0 += 256) {
+  for (int j0 = WPI == 4 ? wave * 64 : 0; j0 < n_total; j0 += 64 * WPI) {
     const int j = j0 + lane, jl = n_total - 1;
     const T* kp = key_row(ksh, kpr, min(j, jl));
-    // the first eight passes' value rows are on their way while the scores form
-    V pre[NC][8];
+    // the first passes' value rows are on their way while the scores form
+    V pre[NC][PF];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
+    for (int t = 0; t < PF; ++t) {
       const T* vp = key_row(vsh, vpr, min(j0 + t * kpp + sub, jl));
 #pragma unroll
       for (int i = 0; i < NC; ++i)
         pre[i][t] = *(const V*)(vp + min(run0 + 64 * i, runs - 1) * VEC);
     }
     float dot = 0.f;
-#pragma unroll 8
+#pragma unroll WPI == 4 ? 8 : 4
     for (int d = 0; d < runs; ++d) {
       const V kv = *(const V*)(kp + d * VEC);
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) dot = fmaf(qs[d * VEC + e], Elt<T>::ld(&kv.v[e]), dot);
+      for (int e = 0; e < VEC; ++e) dot = fmaf(qs[slot][d * VEC + e], Elt<T>::ld(&kv.v[e]), dot);
     }
     const float sc = (j < n_total) ? dot * g.scale_log2 : -INFINITY;
     const float m_new = fmaxf(m, wave_max(sc));
@@ -124,12 +130,12 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(
       for (int e = 0; e < VEC; ++e) acc[i][e] = fmaf(pj, Elt<T>::ld(&vv.v[e]), acc[i][e]);
     };
 #pragma unroll
-    for (int t = 0; t < 8; ++t)
+    for (int t = 0; t < PF; ++t)
       if (t * kpp + sub < cnt)
 #pragma unroll
         for (int i = 0; i < NC; ++i) add(t * kpp + sub, i, pre[i][t]);
 #pragma unroll 4
-    for (int jj = 8 * kpp + sub; jj < cnt; jj += kpp) {
+    for (int jj = PF * kpp + sub; jj < cnt; jj += kpp) {
       const T* vp = key_row(vsh, vpr, j0 + jj);
 #pragma unroll
       for (int i = 0; i < NC; ++i)
@@ -143,29 +149,46 @@ __global__ __launch_bounds__(256) void attn_generic_kernel(
 #pragma unroll
     for (int e = 0; e < VEC; ++e)
       for (int off = lpk; off < 64; off *= 2) acc[i][e] += __shfl_xor(acc[i][e], off);
-  if (sub == 0) {
+  T* out = O + ((long)row * g.H + head) * hd;
+  if constexpr (WPI == 1) {
+    if (sub == 0) {
+      const float inv = 1.f / l;
 #pragma unroll
-    for (int i = 0; i < NC; ++i)
-      if (run0 + 64 * i < runs)
+      for (int i = 0; i < NC; ++i)
+        if (run0 + 64 * i < runs) {
+          V o;
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) os[wave][(run0 + 64 * i) * VEC + e] = acc[i][e];
-  }
-  if (lane == 0) {
-    ms[wave] = m;
-    ls[wave] = l;
-  }
-  __syncthreads();
-  if ((int)threadIdx.x >= hd) return;
-  // wave 0 always had keys; a wave without any has l = 0 and adds nothing
-  const float mm = fmaxf(fmaxf(ms[0], ms[1]), fmaxf(ms[2], ms[3]));
-  float lt = 0.f, ot = 0.f;
+          for (int e = 0; e < VEC; ++e) Elt<T>::st(&o.v[e], acc[i][e] * inv);
+          *(V*)(out + (run0 + 64 * i) * VEC) = o;
+        }
+    }
+  } else {
+    __shared__ float ms[4], ls[4];
+    __shared__ float os[4][256];
+    if (sub == 0) {
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const float f = ls[w] == 0.f ? 0.f : fast_exp2(ms[w] - mm);
-    lt = fmaf(f, ls[w], lt);
-    ot = fmaf(f, os[w][threadIdx.x], ot);
+      for (int i = 0; i < NC; ++i)
+        if (run0 + 64 * i < runs)
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) os[wave][(run0 + 64 * i) * VEC + e] = acc[i][e];
+    }
+    if (lane == 0) {
+      ms[wave] = m;
+      ls[wave] = l;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x >= hd) return;
+    // wave 0 always had keys; a wave without any has l = 0 and adds nothing
+    const float mm = fmaxf(fmaxf(ms[0], ms[1]), fmaxf(ms[2], ms[3]));
+    float lt = 0.f, ot = 0.f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float f = ls[w] == 0.f ? 0.f : fast_exp2(ms[w] - mm);
+      lt = fmaf(f, ls[w], lt);
+      ot = fmaf(f, os[w][threadIdx.x], ot);
+    }
+    Elt<T>::st(out + threadIdx.x, ot / lt);
   }
-  Elt<T>::st(O + ((long)row * g.H + head) * hd + threadIdx.x, ot / lt);
 }
 
 // ------------------------------------------------------------------ MFMA kernels (bf16)

@@ -766,22 +766,48 @@ AttnGeom geom(const alr_config& c) {
   return g;
 }
 
+// Whether a row's keys are shared among a workgroup's four waves.  That shortens the chain
+// of one row; where there are more rows than the CUs hold, waves without keys and the merge
+// only cost.  One-layer prefill, 8192 tokens in sequences of 32 / 256 / 2048: bf16, 16 heads
+// of 96, 1149 / 1452 / 7342 us shared, 417 / 799 / 4493 with a wave per row; fp32, 4 heads of 128,
+// 720 / 877 / 2780 and 577 / 816 / 2836.  With few rows it is the other way round: 2 steps of 8
+// anchors behind 2048 keys take 171 and 326 us (bf16), 275 and 508 (fp32); of 128 anchors with
+// 16 heads of 80, 1188 and 1383 (6 layer steps).
+bool generic_shares_keys(size_t elt, long items, int max_keys, int n_cu) {
+  if (max_keys <= 64) return false;  // only the first wave would have keys
+  if (elt == 4) return items < 16L * n_cu || max_keys > 1024;
+  return items < (max_keys > 512 ? 32L : 8L) * n_cu;
+}
+
 // Whole 16-byte loads of key and value rows where every row starts on one.  A grid
 // dimension holds fewer than 2^32 threads (a launch beyond wraps without an error), so
 // rows past about 2^22 (row, head) pairs go along y.
+//   max_keys: no row of the call has more keys (in the rollout, whose launches a graph may
+//   replay for other anchors, the context's bound).
 template <typename T>
 void launch_attn_generic(const T* q, const T* kc, const T* vc, const T* kp, const T* vp,
                          long priv_rs, int n_priv, const int* row_start, const int* apos, T* out,
-                         int rows, const AttnGeom& g, hipStream_t st) {
+                         int rows, int max_keys, int n_cu, const AttnGeom& g,
+                         hipStream_t st) {
   constexpr int VEC = 16 / (int)sizeof(T);
-  const int per_y = std::min(rows, std::max(1, (1 << 22) / g.H));
-  const dim3 grid((unsigned)(per_y * g.H), (unsigned)((rows + per_y - 1) / per_y));
-  if (g.hd % VEC == 0)
-    attn_generic_kernel<T, VEC><<<grid, 256, 0, st>>>(q, kc, vc, kp, vp, priv_rs, n_priv,
-                                                      row_start, apos, out, rows, g);
-  else
-    attn_generic_kernel<T, 2><<<grid, 256, 0, st>>>(q, kc, vc, kp, vp, priv_rs, n_priv, row_start,
-                                                    apos, out, rows, g);
+  const int rows_y = std::min(rows, std::max(1, (1 << 22) / g.H));
+  const unsigned ny = (unsigned)((rows + rows_y - 1) / rows_y);
+  auto go = [&](auto vec, auto waves) {
+    constexpr int WPI = decltype(waves)::value;
+    const unsigned nx = (unsigned)(((long)rows_y * g.H * WPI + 3) / 4);
+    attn_generic_kernel<T, decltype(vec)::value, WPI><<<dim3(nx, ny), 256, 0, st>>>(
+        q, kc, vc, kp, vp, priv_rs, n_priv, row_start, apos, out, rows, rows_y, g);
+  };
+  const std::integral_constant<int, VEC> wide;
+  const std::integral_constant<int, 2> narrow;
+  const std::integral_constant<int, 4> four;
+  const std::integral_constant<int, 1> one;
+  const bool shared = generic_shares_keys(sizeof(T), (long)rows * g.H, max_keys, n_cu);
+  if (g.hd % VEC == 0) {
+    if (shared) go(wide, four); else go(wide, one);
+  } else {
+    if (shared) go(narrow, four); else go(narrow, one);
+  }
 }
 
 // Column arrangement of the fused QKV weight: for q (n heads of hd), the
@@ -873,7 +899,9 @@ alr_status layer_forward(alr_ctx* ctx, int l, int M, bool decode, int s, float* 
       }
     } else {
       launch_attn_generic<T>(qb, kc, vc, nullptr, nullptr, 0, 0, ctx->at<int>(L.i_rowstart),
-                             nullptr, at, M, g, st);
+                             nullptr, at, M,
+                             *std::max_element(ctx->seq_len.begin(), ctx->seq_len.end()), ctx->n_cu,
+                             g, st);
     }
   } else {
     if (mfma_attn(c)) {
@@ -900,7 +928,8 @@ alr_status layer_forward(alr_ctx* ctx, int l, int M, bool decode, int s, float* 
       }
     } else {
       launch_attn_generic<T>(qb, kc, vc, kp, vp, priv_rs, s, ctx->at<int>(L.i_aseq),
-                             ctx->at<int>(L.i_apos), at, M, g, st);
+                             ctx->at<int>(L.i_apos), at, M, c.max_pos, ctx->n_cu,
+                             g, st);
     }
   }
   }

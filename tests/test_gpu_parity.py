@@ -206,6 +206,25 @@ def test_generic_attention_head_sizes(dtype, hd, H, G):
     assert rep.ok()
 
 
+@pytest.mark.parametrize("dtype,hd,H,G,tokens", [("f32", 64, 1, 1, 63), ("f32", 64, 1, 1, 65),
+                                                 ("f32", 250, 32, 32, 129), ("f32", 32, 4, 2, 1025),
+                                                 ("bf16", 96, 2, 2, 1030), ("bf16", 96, 4, 2, 512)])
+def test_generic_attention_waves_per_row(dtype, hd, H, G, tokens):
+    """Both forms of the generic attention at the edges of its choice on 256 CUs: a wave per row where no
+    row has more than 64 keys (63 items, the last workgroup not full), in bf16 from 2048 items up to 512
+    keys (2048, 512), in fp32 from 4096 up to 1024 (4128, head size 250); four waves per row else."""
+    base = W.get("small_bf16")
+    w = W.scaled(base, f"waves_{dtype}_{hd}_{tokens}", n_layers=2, d_model=256, n_heads=H,
+                 n_kv_heads=G, head_dim=hd, d_ffn=128, vocab=512, feat_layers=(0, 1), dtype=dtype,
+                 n_seq=1, seq_len=tokens, block=3)
+    a_pos = np.array([0, 30, tokens // 2, tokens - 2, tokens - 1], np.int32)
+    inp = W.Inputs(w, W.random_weights(w.shape, hd, scale=0.05, norm_gain="random"),
+                   W.random_tokens(512, (1, tokens), hd, dist="zipf"), np.zeros(5, np.int32), a_pos,
+                   None, None)
+    rep = _full_compare(inp)
+    assert rep.ok()
+
+
 def test_generic_attention_past_one_grid_dimension():
     """More (query, head) pairs than one grid dimension holds workgroups of 256 threads (2^24): the
     last sequences repeat the first ones' tokens, so their rows are bit-identical to rows of the first
