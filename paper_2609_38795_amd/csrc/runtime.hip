@@ -735,17 +735,21 @@ void launch_gemm(alr_ctx* ctx, const T* A, int lda, const T* W, int ldw, int M, 
     }
   } else {
     const int tm = (M + GF_M - 1) / GF_M, tn = (N + GF_N - 1) / GF_N;
-    // 64x64 tiles pay where they fill the CUs (M = 1200, N = 1024, K = 128: 304 tiles).
-    // Else 8 x 64 ones, or 8 x 16 where even those leave three CUs of four idle (the
-    // logits' statistics need whole 64-column groups).
-    if (tm * tn >= ctx->n_cu) {
+    const int groups = N / 64;
+    const long rows = ((long)M + GFS_M - 1) / GFS_M;
+    // 8 x 64 tiles, one on a CU at a time, while two rounds of them hold the product, and 8 x 16 ones
+    // where even those leave three CUs of four idle (the logits' statistics need whole
+    // 64-column groups).  64x64 tiles beyond: a round of the small ones takes 0.4 of the time
+    // that all 64x64 tiles take together, up to one per CU (K = 1024, N = 1024: 23.2 us for 128
+    // rows, 45 for 200 and 256, 89 for 400, against 60 for any of these; at K = 128 7.3, 8.0,
+    // 14.9 against 10.2).
+    if (groups * rows > 2L * ctx->n_cu) {
       gemm_f32_kernel<TAG, Epi><<<tm * tn, 256, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
     } else {
-      const int groups = N / 64, rows = (M + GFS_M - 1) / GFS_M;
       auto small = [&](auto pairs) {
         constexpr int P = decltype(pairs)::value;
         gemm_f32_small_kernel<TAG, P, Epi>
-            <<<dim3(groups * (32 / P), rows), 512, 0, st>>>(A, lda, W, ldw, M, N, K, epi);
+            <<<dim3(groups * (32 / P), (unsigned)rows), 512, 0, st>>>(A, lda, W, ldw, M, N, K, epi);
       };
       if constexpr (std::is_same<Epi, EpiLogits>::value)
         small(std::integral_constant<int, 32>{});

@@ -81,10 +81,12 @@ def test_gemm_wide(M, N, K, tile):
     assert err <= 2e-5 * np.sqrt(K) * 4, err
 
 
-@pytest.mark.parametrize("M,N,K", [(7, 64, 64), (8, 128, 512), (9, 192, 320), (4097, 256, 64)])
+@pytest.mark.parametrize("M,N,K", [(7, 64, 64), (8, 128, 512), (9, 192, 320), (1024, 256, 64),
+                                   (1025, 256, 64), (4097, 256, 64)])
 def test_gemm_f32_few_tiles(M, N, K):
     """fp32 products around the 8-row tiles of the kernel whose waves share K (one wave with work,
-    K not a multiple of the waves' share), and the first size that goes to 64x64 tiles on 256 CUs."""
+    K not a multiple of the waves' share), the last size that takes it (512 tiles) and the first that goes to
+    64x64 tiles on 256 CUs, and one with more of those than CUs."""
     _print(f"gemm f32 {M}x{N}x{K}")
     g = torch.Generator().manual_seed(M + K)
     a, w = (torch.randn(s, generator=g).cuda() for s in ((M, K), (N, K)))
