@@ -425,7 +425,11 @@ __device__ __forceinline__ void block_pop8(float (&tv)[L], int (&ti)[L], Top8& o
 __device__ __forceinline__ float row_top8(const LogitPart* pr, int n, const float* z, float m,
                                           Top8Scratch& sc) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  {
+  if (n <= ALR_K_TOP) {  // every group is one of the eight (256 rows of 512 columns: 16.3 -> 10.3 us)
+    if (threadIdx.x < ALR_K_TOP)
+      sc.groups.i[threadIdx.x] = (int)threadIdx.x < n ? (int)threadIdx.x : 0x7FFFFFFF;
+    __syncthreads();
+  } else {
     float tv[ALR_K_TOP];
     int ti[ALR_K_TOP];
 #pragma unroll
