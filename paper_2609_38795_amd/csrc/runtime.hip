@@ -1241,17 +1241,46 @@ alr_status upload(alr_ctx* ctx, void* dst, const void* src, size_t bytes, hipStr
   return ALR_OK;
 }
 
+// Columns a panel of the corpus labels' product may have for D rows: whole 256-column
+// tiles where they fit the workspace's logit rows, and at least one 64-column group.
+int label_panel_cols(const alr_ctx* ctx, int D) {
+  const long V = ctx->cfg.vocab, fit = (long)ctx->lim.max_anchors * V / D;
+  const long unit = fit >= 256 ? 256 : 64;
+  return (int)std::min<long>(V, std::max<long>(unit, fit / unit * unit));
+}
+
+// Whether labelling D distinct positions, panel by panel, takes less time than n anchors
+// slot by slot.  Either way a step costs its launches, a statistics pass (less where it has at
+// most eight 64-column groups), the product's K loop, and its share of the products' weights
+// and operations.  The constants are a fit over vocabularies of 512 to 152064, 4 to 1024 anchors,
+// 2 to 16 slots, dense and without overlap (84 cases): the choice costs 0.2% over the better one in
+// the mean, 27% at worst.  Measured (us, slots and panels): V = 32000, d 1024, 1024 anchors x
+// 16: 1775 and 216 with D = 1144, 745 with 4192, 5959 with 16384; V = 128256, d 4096, 192 x 16 with
+// D = 3072: 5328 and 3984; V = 512, 4 x 2: 64 and 71.
+bool label_panels_pay(const alr_ctx* ctx, int n, int block, int D) {
+  const alr_config& c = ctx->cfg;
+  const bool bf = c.dtype == ALR_BF16;
+  const double V = c.vocab, d = c.d_model, weights = V * d * (bf ? 2 : 4);
+  const double read_us = weights / (weights < 2e8 ? 9.4e6 : 6.6e6);  // last-level cache or HBM
+  auto product = [&](double rows) { return read_us + 2 * rows * V * d / (bf ? 1.3e9 : 3e7); };
+  auto step = [&](double rows, int width) {
+    return (width <= 512 ? 16 + 0.008 * rows : 24 + 0.012 * rows) + d / 256;
+  };
+  const int cols = label_panel_cols(ctx, D), panels = (c.vocab + cols - 1) / cols;
+  return 10 + panels * step(D, cols) + product(D) < block * (2 + step(n, c.vocab) + product(n));
+}
+
 // Corpus labels: the prefill's final-norm rows at a + s through the output head,
 // the corpus token's log-prob, then the gates.  Without full log-prob rows every
-// distinct position is labelled once, all of them in one product per panel of
+// distinct position may be labelled once, all of them in one product per panel of
 // columns (LabelState); a panel is as wide as the workspace's logit rows
-// (max_anchors x vocab values) allow, so there are never more products than
-// slots.  At 2 x 96 anchors x 16 slots of 2 x 1024 tokens (d 3584, vocab 152064)
-// that is 1,206 rows in 7 products instead of 16 products of 192 rows that each
-// read the whole 1.09 GB head (9.5 -> 1.7 ms per call).  Full log-prob rows go slot by slot, where the
-// product writes the caller's rows itself.  So does a call that is captured: a replay takes
-// the anchors from the tables as they are then, and a list of positions made for others
-// would send the expansion to rows that were never labelled.
+// (max_anchors x vocab values) allow.  At 2 x 96 anchors x 16 slots of 2 x 1024 tokens
+// (d 3584, vocab 152064) that is 1,206 rows in 7 products instead of 16 products of 192 rows
+// that each read the whole 1.09 GB head (9.2 -> 1.4 ms per call).  Where slots share few
+// positions it goes slot by slot (label_panels_pay), as it does with full log-prob rows, which
+// that product writes itself, and in a call that is captured: a replay takes the
+// anchors from the tables as they are then, and a list of positions made for others would
+// send the expansion to rows that were never labelled.
 template <typename T>
 alr_status corpus_impl(alr_ctx* ctx, int n, int block, const LabelDst& out, float* corpus_logp,
                        float* gate_soft, float* gate_hard, hipStream_t st) {
@@ -1260,9 +1289,10 @@ alr_status corpus_impl(alr_ctx* ctx, int n, int block, const LabelDst& out, floa
   const int d = c.d_model, V = c.vocab;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   ALR_HIP(ctx, hipStreamIsCapturing(st, &cap));
-  const bool by_slot = out.logprobs != nullptr || cap != hipStreamCaptureStatusNone;
+  const int D = (int)ctx->h_urow.size();
+  const bool by_slot = out.logprobs != nullptr || cap != hipStreamCaptureStatusNone ||
+                       !label_panels_pay(ctx, n, block, D);
   if (!by_slot) {
-    const int D = (int)ctx->h_urow.size();
     const int* urow = ctx->at<int>(L.i_urow);
     LabelState* state = ctx->at<LabelState>(L.label_state);
     const alr_status stt = upload(ctx, ctx->at<int>(L.i_urow), ctx->h_urow.data(), (size_t)D * 4, st);
@@ -1270,10 +1300,7 @@ alr_status corpus_impl(alr_ctx* ctx, int n, int block, const LabelDst& out, floa
     label_rows_kernel<T><<<D, 256, 0, st>>>(ctx->at<T>(L.xnorm), ctx->at<T>(L.hf_store), urow,
                                             ctx->at<int>(L.i_uidx), d);
     ALR_LAUNCHED(ctx, "corpus rows");
-    // whole 256-column tiles where they fit, and at least one 64-column group
-    const long fit = (long)ctx->lim.max_anchors * V / D;
-    const long unit = fit >= 256 ? 256 : 64;
-    const int wide = (int)std::min<long>(V, std::max<long>(unit, fit / unit * unit));
+    const int wide = label_panel_cols(ctx, D);
     for (int c0 = 0; c0 < V; c0 += wide) {
       const int w = std::min(wide, V - c0);
       EpiLogits el;

@@ -249,6 +249,32 @@ def test_corpus_labels_panels_match_rows(dtype, vocab, block, max_anchors):
     eng.close()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("stride,block,launches", [(10, 2, 2), (1, 8, 3)])
+def test_corpus_labels_go_by_slot_or_by_position(dtype, stride, block, launches):
+    """Six anchors over a vocabulary of 448, so that the logit rows hold 6 x 448 values: 12 positions
+    without overlap would take 3 panels of 192 columns for 2 slots, 13 shared ones take 3 for 8.  The
+    number of output-head products tells the path; labels against the form with log-prob rows."""
+    base = W.get("tiny_fp32")
+    w = W.scaled(base, "labels_path", vocab=448, dtype=dtype, n_seq=1, seq_len=70, anchor_hi=69,
+                 block=block)
+    a_seq, a_pos = np.zeros(6, np.int32), np.arange(3, 3 + 6 * stride, stride, dtype=np.int32)
+    inp = W.Inputs(w, W.random_weights(w.shape, 5, scale=0.1), W.random_tokens(448, (1, 70), 6),
+                   a_seq, a_pos, None, None)
+    eng = make_engine(inp, max_anchors=6)
+    prefill(eng, inp)
+    binding.profile_start(eng, "lm_gemm", 64)
+    a = eng.corpus_labels(a_seq, a_pos, block)
+    assert binding.profile_stop(eng)[1] == launches
+    b = eng.corpus_labels(a_seq, a_pos, block, want_logprobs=True)
+    for k in ("argmax", "top_ids", "gate_hard"):
+        assert torch.equal(a[k], b[k]), k
+    for k in ("top_logp", "tail", "corpus_logp", "gate_soft"):
+        # fp32 sums over the vocabulary in another grouping: a few ulp of the log-sum-exp
+        np.testing.assert_allclose(_np(a[k]), _np(b[k]), rtol=4e-6, atol=4e-6, err_msg=k)
+    eng.close()
+
+
 @pytest.mark.parametrize("name", ["tiny_fp32", "small_bf16"])
 def test_top8_passes_nan_logits_over(name):
     """NaN rows of the output head (two of them, and a whole 64-column group): log-probs and tail
