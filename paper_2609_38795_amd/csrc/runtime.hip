@@ -1822,7 +1822,7 @@ alr_status prepare_anchors(alr_ctx* ctx, int32_t n_anchor, const int32_t* anchor
   ctx->h_dwork.clear();
   ctx->h_groups.clear();
   ctx->h_grprow.assign(n, 0);
-  if (rollout) {
+  if (rollout && block > 1 && c.n_layers > 0) {  // slot 0 attends to nothing
     if (mfma_attn(c)) {
       std::vector<int> sq_sorted(n);
       for (int r = 0; r < n; ++r) sq_sorted[r] = anchor_seq[order[r]];
