@@ -85,7 +85,7 @@ typedef enum {
  * is the width of an output-head product that covers a panel of the vocabulary (corpus
  * labels), a multiple of 64; 0, and at every other site, the site's own.  Writes the kernel to
  * *kernel_out (0 = 32x64, 1 = 64x64, 2 = 128x64, 3 = 128x128 tiles of the few-row kernel, 4 =
- * 128x128 LDS-staged, 5 = 256x256), its K slices, summed by a reduce, to *splits_out, and the K
+ * 128x128 LDS-staged, 5 = 256x256, 6 = 64x128 LDS-staged), its K slices, summed by a reduce, to *splits_out, and the K
  * slices of the tiles past the last full round to *tail_out (1: not sliced).
  * ALR_E_UNSUPPORTED for fp32, ALR_E_INVALID_ARG for a site without a GEMM or bad counts, the
  * statuses of alr_check_config otherwise. */

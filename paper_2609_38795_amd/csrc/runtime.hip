@@ -496,11 +496,16 @@ bool launch_splitk_resid_norm(alr_ctx* ctx, int S, int M, int N, const EpiResid&
 // what a tile costs besides its K loop; slices add the fp32 partials they write
 // and re-read (4.2 TB/s) and a second launch, unless that is the reduce which
 // carries the following RMSNorm (3.4 us: M = 7, N = 1536, K = 1024 takes 6.4 us whole,
-// 4.0 + 3.1 sliced; M = 256 11.5 whole, 6.4 + 3.7 sliced).  The constants are fits over
-// M = 7 .. 8192, N = 1024 .. 37888, K = 1024 .. 18944 (weights rotated through more
-// than the last-level cache).  A step of the 256x256 kernel takes longer the more CUs
-// run it, as the clock falls: 1.03 us on half of them, 1.35 us on all.  Where the
-// lines lie:
+// 4.0 + 3.1 sliced; M = 256 11.5 whole, 6.4 + 3.7 sliced).  The constants are fits to
+// products that store plain fp32 rows, M = 7 .. 8192, N = 64 .. 37888, K = 64 .. 18944
+// (weights rotated through more than the last-level cache).  The epilogues of the model are
+// in them for the 256x256 kernel alone (epi_us); with theirs the 128x128 LDS-staged
+// tiles take longer than estimated (rollout O of 1024 x 4096 x 4096 50 us for 39, down of
+// 8192 x 1024 x 2816 68 for 56, O of 8192 x 1024 x 1024 32 for 23).  A step of the 256x256
+// kernel takes longer the more CUs run it, as the clock falls: 1.03 us on half of them,
+// 1.35 us on all; so does, less, one of the 64x128 LDS-staged tiles, which look two steps
+// ahead and fall behind where the weights come from HBM (more than 20 MB) or their tiles are
+// dealt to the XCDs in no order (a count that is no multiple of 8).  Where the lines lie:
 //   M <= 64 streams weights, so the 32- and 64-row tiles win, and up to 128 rows two
 //   64-row tiles do where 128-row ones leave CUs idle (M = 128, N = 8064, K = 4096: 26
 //   us against 36); else at M = 128 the 128-row ring tiles do (N = 28672, K = 4096:
@@ -508,8 +513,11 @@ bool launch_splitk_resid_norm(alr_ctx* ctx, int S, int M, int N, const EpiResid&
 //   the 256x256 tiles, sliced so that they fill the CUs (M = 1024, N = 6144, K = 4096:
 //   2 slices 48 us, 128x128 63; M = 2048: unsliced 83, 128x128 117).  128x128 LDS-staged
 //   tiles remain where 256x256 ones would leave CUs idle and K is too short to slice
-//   (M = 8192, N = 1024, K = 1024: 23.6 against 25.7 us).
-enum class Gemm { ring32, ring64, ring128x64, ring128, lds128, wide };
+//   (M = 8192, N = 1024, K = 1024: 23.6 against 25.7 us), 64x128 ones above 128 rows where
+//   the weights are small and larger tiles leave CUs idle (N = 1024, K = 2816: M = 300 18.5
+//   us against 20.0 for 128x64 ring tiles, M = 2048 22.0 against 27.0; M = 8192, N = 256, K
+//   = 512 7.8 against 13.9: past 1024 rows the ring's 128x64 tiles read A once per XCD).
+enum class Gemm { ring32, ring64, ring128x64, ring128, lds128, wide, lds64 };
 struct GemmPlan {
   Gemm kernel;
   int bm, bn, splits;
@@ -530,24 +538,37 @@ GemmPlan pick_gemm(int M, int N, int K, int n_cu, size_t split_bytes, bool norm_
   static const Kern kerns[] = {
       {Gemm::ring32, 32, 64, 0.26f, 2.f},      {Gemm::ring64, 64, 64, 0.34f, 2.f},
       {Gemm::ring128x64, 128, 64, 0.47f, 2.f}, {Gemm::ring128, 128, 128, 0.57f, 3.f},
-      {Gemm::lds128, 128, 128, 0.58f, 2.3f},   {Gemm::wide, 256, 256, 0.f, 10.f}};
+      {Gemm::lds128, 128, 128, 0.58f, 2.3f},   {Gemm::lds64, 64, 128, 0.33f, 3.4f},
+      {Gemm::wide, 256, 256, 0.f, 10.f}};
   GemmPlan best{Gemm::ring32, 0, 0, 0};
   float best_us = 0.f;
   for (const Kern& k : kerns) {
     // the smallest row tile that holds M, or tiles of 128 rows and more
-    if (k.bm == 32 ? M > 32 : (k.bm == 64 ? M <= 32 || M > 128 : M <= 64)) continue;
-    if (k.k == Gemm::lds128 && M <= FEW_ROWS) continue;  // the ring kernel of that tile is faster
+    if (k.k == Gemm::lds64 ? M <= 128
+                           : (k.bm == 32 ? M > 32 : (k.bm == 64 ? M <= 32 || M > 128 : M <= 64)))
+      continue;
+    if (k.k == Gemm::ring128x64 && M > 1024) continue;
     const long t = (long)((M + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn);
+    // with few rows the ring kernel of that tile is faster, but for an epilogue that the second
+    // workgroup on the CU covers (output head of M = 256, N = 32000, K = 1024: 31.7 against 35.0 us)
+    if (k.k == Gemm::lds128 && (M <= 128 || (M <= FEW_ROWS && (t <= n_cu || epi_us == 0.f))))
+      continue;
     for (int S = 1; S <= 8; S *= 2) {
       if (k.k == Gemm::wide && K / S < 192) continue;
-      if (S > 1 && (k.k == Gemm::lds128 || t * S > n_cu || K % (64 * S) != 0 || K / S < 256 ||
+      if (S > 1 && (k.k == Gemm::lds128 || k.k == Gemm::lds64 || t * S > n_cu || K % (64 * S) != 0 || K / S < 256 ||
                     (size_t)S * M * N * 4 > split_bytes || (S == 8 && (N > 4096 || M > FEW_ROWS))))
         continue;
       const long rounds = (t * S + n_cu - 1) / n_cu;
       const float busy = std::min(1.f, (float)(t * S) / n_cu);
-      const float step = k.k == Gemm::wide ? 0.7f + 0.65f * busy : k.step_us;
+      float step = k.k == Gemm::wide ? 0.7f + 0.65f * busy : k.step_us;
+      if (k.k == Gemm::lds64) {
+        step += 0.1f * busy + ((double)N * K * 2 > 2e7 ? 0.12f : 0.f);
+        if (t >= 128 && t % 8 != 0) step *= 1.1f;
+      }
       float us = (float)rounds * ((float)(K / 64 / S) * step + k.tile_us +
                                   (k.k == Gemm::wide && S == 1 ? epi_us : 0.f));
+      if (k.k == Gemm::lds64 && rounds > 1)  // two on a CU at a time
+        us = 2.f + (float)rounds * ((float)(K / 64) * (step - 0.07f) + 2.2f);
       if (S > 1) us += (float)S * M * N * (4.f / 4.2e6f) + (norm_follows ? 0.f : 3.4f);
       int tail = 1;
       const long left = t % n_cu;
@@ -594,6 +615,16 @@ void launch_plan(const GemmPlan& p, int n_cu, const bf16* A, int lda, const bf16
               <<<tm * tn, 256, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
         else
           gemm_bf16_kernel<TAG, 128, 128, 2, 2, 32, 2, Epi>
+              <<<tm * tn, 256, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
+      }
+      break;
+    case Gemm::lds64:
+      if constexpr (!has_set_split<Epi>::value) {  // never sliced
+        if (K % 128 == 0)
+          gemm_bf16_kernel<TAG, 64, 128, 2, 2, 64, 2, Epi>
+              <<<tm * tn, 256, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
+        else
+          gemm_bf16_kernel<TAG, 64, 128, 2, 2, 32, 4, Epi>
               <<<tm * tn, 256, 0, st>>>(A, lda, W, ldw, M, N, K, tm, tn, epi);
       }
       break;

@@ -6,7 +6,7 @@ import pytest
 
 from paper_2609_38795_amd import binding, workloads as W
 
-WIDE = 5
+RING128X64, LDS128, WIDE, LDS64 = 2, 4, 5, 6
 
 
 def _plan(shape, site, rows, cols=0, tokens=8192, anchors=1024, n_cu=256):
@@ -36,6 +36,17 @@ def test_sliced_last_round_depends_on_the_device():
     s = W.get("vl_prefix_7b").shape
     assert _plan(s, "prefill_down", 10900, tokens=10900) == (WIDE, 1, 2)
     assert _plan(s, "prefill_down", 10900, tokens=10900, n_cu=301) == (WIDE, 1, 1)
+
+
+def test_where_64x128_tiles_are_taken():
+    """1B-like prefill: above 128 rows while larger tiles leave CUs idle and the weights are small; not
+    for the 33 MB of an 8B-like layer's O."""
+    s = W.get("small_bf16").shape
+    plan = lambda rows, shape=s, site="prefill_qkv": _plan(shape, site, rows, anchors=1)[0]
+    assert plan(128) != LDS64 and plan(300) == LDS64 and plan(600) == LDS64
+    assert plan(2048) == LDS128 and plan(32768) == WIDE
+    assert plan(2048, site="prefill_o") == LDS64  # 256 tiles of K = 1024
+    assert plan(300, W.get("llama8b_like").shape, "prefill_o") == RING128X64
 
 
 def test_plan_errors():

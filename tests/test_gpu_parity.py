@@ -277,14 +277,14 @@ def test_generic_attention_tile_of_minus_infinity():
     np.testing.assert_allclose(row, want, rtol=0, atol=1e-5 * np.abs(want).max())
 
 
-@pytest.mark.parametrize("hd,H,G,tokens,kernel", [(36, 32, 16, 90, 2), (100, 16, 16, 90, 2),
-                                                  (10, 64, 32, 90, 2), (50, 32, 32, 90, 2),
-                                                  (50, 32, 32, 400, 4), (50, 32, 32, 1000, 5)])
+@pytest.mark.parametrize("hd,H,G,tokens,kernel", [(36, 32, 16, 90, 6), (100, 16, 16, 90, 6),
+                                                  (10, 64, 32, 90, 6), (50, 32, 32, 64, 1),
+                                                  (50, 32, 32, 200, 4), (50, 32, 32, 1000, 5)])
 def test_rope_pairs_across_heads(hd, H, G, tokens, kernel):
     """bf16 head sizes whose half is no multiple of 4 (36, 100) or odd (50, 10): runs of four and
     pairs of neighbouring columns of the fused QKV product then cross from one head into the next,
     in the split-K reduce of the rollout and in the row epilogues of the prefill (the few-row
-    kernel, the LDS-staged one, 256x256 tiles)."""
+    kernel, the LDS-staged one of both tiles, 256x256 tiles)."""
     base = W.get("small_bf16")
     w = W.scaled(base, f"pairs_{hd}_{tokens}", n_layers=2, d_model=2048, n_heads=H, n_kv_heads=G,
                  head_dim=hd, d_ffn=128, vocab=512, feat_layers=(0, 1), n_seq=2,
@@ -294,7 +294,7 @@ def test_rope_pairs_across_heads(hd, H, G, tokens, kernel):
     assert splits > 1
     assert binding.gemm_plan(w.shape, lim, "prefill_qkv", w.n_tokens, n_cu=n_cu())[0] == kernel
     a_seq = np.array([0, 0, 1, 1, 1], np.int32)
-    a_pos = np.array([0, 40, 63, 64, tokens - 1], np.int32)
+    a_pos = np.array([0, 40, 33, tokens // 2, tokens - 1], np.int32)
     inp = W.Inputs(w, W.random_weights(w.shape, hd, scale=0.02, norm_gain="random"),
                    W.random_tokens(512, (2, tokens), hd, dist="zipf"), a_seq, a_pos, None, None)
     rep = _full_compare(inp)
