@@ -433,8 +433,10 @@ struct ProfScope {
 };
 
 // Sum of the S fp32 K-slice partials of an M x N product, then the real
-// epilogue; the slice counts the planner picks (2, 4) get kernels that load
-// every partial before the first add.
+// epilogue.  The counts that pick_gemm takes for any product (2, 4) get kernels that load
+// every partial before the first add, and so does 8 where the epilogue takes four columns
+// (QKV) or carries the norm (launch_splitk_resid_norm); what else is cut into 8 (gate and up of
+// few rows) adds them in a loop.
 template <class Epi>
 void launch_splitk_reduce(const float* part, long sstride, int S, int M, int N, const Epi& epi,
                           hipStream_t st) {

@@ -94,14 +94,14 @@ def test_plan_of_the_headline_workload():
     assert ct == 27 and len(items) == 584 and span == 30
 
 
-@pytest.mark.parametrize("n_cu,least", [(256, 2), (22, 2), (21, 4)])
-def test_plan_of_few_tiles(n_cu, least):
-    """44 tiles (11 of the one anchor group, 4 kv heads): chunks of 2 tiles where two tiles per CU
-    are at least as many, of no fewer than 4 elsewhere."""
+@pytest.mark.parametrize("n_cu,chunk", [(256, 2), (22, 2), (21, 4)])
+def test_plan_of_few_tiles(n_cu, chunk):
+    """44 tiles (11 of the one anchor group, 4 kv heads): chunks of 2 tiles up to the last device for which
+    two tiles per CU are at least as many (22 CUs), of no fewer than 4 on the next."""
     shape = W.get("small_bf16").shape
     ct, _, _ = _check_plan(shape, 1024, n_cu, [701], np.zeros(7, np.int32),
                            np.arange(640, 696, 8, dtype=np.int32))
-    assert ct == 2 if least == 2 and n_cu == 256 else ct >= least
+    assert ct == chunk
 
 
 def test_plan_errors():

@@ -23,8 +23,8 @@ import numpy as np
 import pytest
 
 import oracle as O
-from paper_2609_38795_amd import workloads as W
-from gpu_util import make_engine, prefill
+from paper_2609_38795_amd import binding, workloads as W
+from gpu_util import make_engine, n_cu, prefill
 
 pytestmark = pytest.mark.gpu
 
@@ -108,3 +108,56 @@ def test_layer_local_rollout_8b_width(which):
         else:
             x = np.concatenate([pre[r0:r0 + a + 1, layer - 1], roll[i, 1:, layer - 1]], axis=0)
         _check(inp, w, layer, x, roll[i, 1:, layer], rows, f"rollout anchor {a}")
+
+
+def test_layer_local_sliced_last_round():
+    """8,300 tokens in sequences of 40 to 160 at d 4096, F 3072: on 256 CUs the tiles past the last full round
+    of every prefill product are cut over K (their partial sums in activation buffers that must be idle
+    at that site), and so are those of the output head of 768 anchors over a vocabulary of 22528.  Sequences whose rows
+    lie in the first, a middle and the last row tiles against the oracle layer by layer, every anchor's
+    log-probs against the head in float64."""
+    rng = np.random.default_rng(5)
+    lens = []
+    while sum(lens) < 8300 - 160:
+        lens.append(int(rng.integers(40, 160)))
+    lens.append(8300 - sum(lens))
+    base = W.get("llama8b_like")
+    w = W.scaled(base, "sliced_round", n_layers=2, feat_layers=(0, 1), d_ffn=3072, vocab=22528,
+                 n_seq=len(lens), seq_len=max(lens), anchors_per_seq=1, block=1)
+    lim = binding.make_limits(8300, len(lens), 768, 1)
+    for site in ("prefill_qkv", "prefill_o", "prefill_gu", "prefill_down", "lm_gemm"):
+        kernel, splits, tail = binding.gemm_plan(w.shape, lim, site, 768 if site == "lm_gemm" else 8300,
+                                                 n_cu=n_cu())
+        assert (kernel, splits) == (5, 1) and tail > 1, (site, kernel, splits, tail)
+    wts = W.random_weights(w.shape, 81, scale=0.02, norm_gain="random")
+    tok = W.random_tokens(22528, (8300,), 82, dist="zipf")
+    off = np.concatenate([[0], np.cumsum(lens)])
+    a_tok = rng.integers(0, 8300, 768)
+    a_seq = (np.searchsorted(off, a_tok, side="right") - 1).astype(np.int32)
+    a_pos = (a_tok - off[a_seq]).astype(np.int32)
+    eng = binding.Engine(w.shape, wts, max(lens) + 1, lim, device=torch.device("cuda:0"))
+    fo = torch.empty((8300, 2, 4096), dtype=torch.float32, device=eng.device)
+    eng.prefill(torch.from_numpy(tok.astype(np.int32)).to(eng.device), lens, None, None, fo)
+    _, lp, _ = eng.rollout(a_seq, a_pos, 1)
+    torch.cuda.synchronize()
+    print(f"sliced last rounds: {len(lens)} sequences prefilled, 768 anchors", flush=True)
+    # head: the final norm's bf16 rows of the GPU's last layer, products in float64
+    h = fo[torch.from_numpy(a_tok).cuda(), 1].double()
+    gain = torch.from_numpy(O.Params(wts).get("final_norm")).double().cuda()
+    hf = (h * torch.rsqrt((h * h).mean(1, keepdim=True) + w.shape.rms_eps) * gain).bfloat16().double()
+    head = torch.from_numpy(O.Params(wts).get("lm_head")).double().cuda()
+    want = torch.log_softmax(hf @ head.T, -1)
+    err = float((lp[:, 0].double() - want).abs().max())
+    print(f"  head: log-prob max-abs {err:.2e}", flush=True)
+    # a norm output on a rounding boundary may go either way: 2^-8 of one of 4096 products
+    assert err <= 2.0 ** -8 * float(hf.abs().max() * head.abs().max()) * 2, err
+    inp = W.Inputs(w, wts, None, None, None, None, None)
+    P = O.Params(wts)
+    pre = fo.cpu().numpy().astype(np.float64)
+    for i in (0, len(lens) // 2, len(lens) - 2, len(lens) - 1):
+        x = O.embed_rows(P, tok[off[i]:off[i + 1]])
+        for layer in range(2):
+            got = pre[off[i]:off[i + 1], layer]
+            _check(inp, w, layer, x, got, slice(None), f"sequence {i}")
+            x = got
+    eng.close()
