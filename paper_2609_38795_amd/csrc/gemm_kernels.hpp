@@ -53,7 +53,10 @@ __device__ __forceinline__ f32x2 pair_rows(int odd, float x_r, float x_r1) {
   return odd ? f32x2{x, x_r1} : f32x2{x_r, x};
 }
 
-template <typename OutT>
+// PAIRS: half a head is even, so that two neighbouring columns share one.  Else (head size
+// 50) rows() takes its elements one by one; a branch between the two would cost the 256x256
+// kernel 22 more spilled scalar registers.
+template <typename OutT, bool PAIRS = true>
 struct EpiQKV {
   OutT* q;            // [M, H*hd]
   OutT* k;            // row r -> k + r*kv_rs
@@ -154,7 +157,7 @@ struct EpiQKV {
   // rows need (cos/sin, or the V^T columns) is issued before any store, so the
   // block costs one memory round trip.  Looking the rows' positions up here first
   // made it two, and in the 256x256 kernel, where nothing hides them, the prefill
-  // projection (32768 x 6144 x 4096) took 1.37 ms instead of 1.27.  Four consecutive,
+  // projection (32768 x 6144 x 4096) took 1.37 ms instead of 1.28.  Four consecutive,
   // 4-aligned columns of the transposed V cache go out
   // as one 8-byte store per column (bf16).
   static constexpr bool by_rows = true;
@@ -166,8 +169,7 @@ struct EpiQKV {
     int r[NR];
 #pragma unroll
     for (int t = 0; t < NR; ++t) r[t] = rb + QS * (t >> 2) + (t & 3);
-    if (c < qd + kd && (half & 1)) {
-      // the two columns of a lane pair may lie in different heads (head size 50)
+    if (!PAIRS && c < qd + kd) {
 #pragma unroll
       for (int t = 0; t < NR; ++t)
         if (r[t] < M) (*this)(r[t], c, lo[t], hi[t]);
@@ -190,7 +192,7 @@ struct EpiQKV {
 #pragma unroll
       for (int t = 0; t < NR; ++t) w[t] = rope[(long)min(r[t], M - 1) * half + i];
       // The two lanes of a column pair (i even, i+1 in the same head, half being
-      // even here) trade one value of each half per two rows, so the even lane
+      // even) trade one value of each half per two rows, so the even lane
       // writes row r at i, i+1 and the odd lane row r+1: one store of two
       // elements per half instead of two single-element stores.
       const int odd = c & 1;

@@ -890,33 +890,38 @@ alr_status layer_forward(alr_ctx* ctx, int l, int M, bool decode, int s, float* 
   if (!normed_in)
     rmsnorm_kernel<T><<<M, 256, 0, st>>>(resid, reinterpret_cast<const T*>(lw + L.l_anorm), xn, d,
                                          c.rms_eps);
-  EpiQKV<T> eq;
-  eq.q = qb;
-  eq.rope = ctx->at<f32x2>(L.rope_rows);
-  eq.H = H;
-  eq.G = G;
-  eq.hd = hd;
-  eq.vt_col = nullptr;
-  eq.vt_stride = 0;
-  if (!decode) {
-    eq.k = kc;
-    eq.v = vc;
-    eq.kv_rs = kvd;
-    if (L.vt_stride) {
-      eq.vt_col = ctx->at<int>(L.i_vtcol);
-      eq.vt_stride = (long)L.vt_stride;
+  auto qkv = [&](auto eq) {
+    eq.q = qb;
+    eq.rope = ctx->at<f32x2>(L.rope_rows);
+    eq.H = H;
+    eq.G = G;
+    eq.hd = hd;
+    eq.vt_col = nullptr;
+    eq.vt_stride = 0;
+    if (!decode) {
+      eq.k = kc;
+      eq.v = vc;
+      eq.kv_rs = kvd;
+      if (L.vt_stride) {
+        eq.vt_col = ctx->at<int>(L.i_vtcol);
+        eq.vt_stride = (long)L.vt_stride;
+      }
+    } else {
+      eq.k = kp + (long)(s - 1) * kvd;
+      eq.v = vp + (long)(s - 1) * kvd;
+      eq.kv_rs = priv_rs;
     }
-  } else {
-    eq.k = kp + (long)(s - 1) * kvd;
-    eq.v = vp + (long)(s - 1) * kvd;
-    eq.kv_rs = priv_rs;
-  }
-  if (decode)
-    launch_gemm<ALR_PROF_DECODE_QKV, T>(ctx, xn, d, reinterpret_cast<const T*>(lw + L.l_qkv), d, M,
-                                        qd + 2 * kvd, d, eq, st);
+    if (decode)
+      launch_gemm<ALR_PROF_DECODE_QKV, T>(ctx, xn, d, reinterpret_cast<const T*>(lw + L.l_qkv), d,
+                                          M, qd + 2 * kvd, d, eq, st);
+    else
+      launch_gemm<ALR_PROF_PREFILL_QKV, T>(ctx, xn, d, reinterpret_cast<const T*>(lw + L.l_qkv), d,
+                                           M, qd + 2 * kvd, d, eq, st);
+  };
+  if (std::is_same<T, bf16>::value && hd % 4 != 0)
+    qkv(EpiQKV<T, !std::is_same<T, bf16>::value>{});
   else
-    launch_gemm<ALR_PROF_PREFILL_QKV, T>(ctx, xn, d, reinterpret_cast<const T*>(lw + L.l_qkv), d,
-                                         M, qd + 2 * kvd, d, eq, st);
+    qkv(EpiQKV<T>{});
   ALR_LAUNCHED(ctx, "qkv gemm");
 
   const AttnGeom g = geom(c);
