@@ -518,7 +518,9 @@ bool launch_splitk_resid_norm(alr_ctx* ctx, int S, int M, int N, const EpiResid&
 //   (M = 8192, N = 1024, K = 1024: 23.6 against 25.7 us), 64x128 ones above 128 rows where
 //   the weights are small and larger tiles leave CUs idle (N = 1024, K = 2816: M = 300 18.5
 //   us against 20.0 for 128x64 ring tiles, M = 2048 22.0 against 27.0; M = 8192, N = 256, K
-//   = 512 7.8 against 13.9: past 1024 rows the ring's 128x64 tiles read A once per XCD).
+//   = 512 7.8 against 13.9: past 1024 rows the ring's tiles read A once per XCD), and where
+//   K is short (K = 128, M = 1654: QKV of N = 256 6.9 us against 10.7 for 128x128, O of N =
+//   128 4.8 against 6.4).
 enum class Gemm { ring32, ring64, ring128x64, ring128, lds128, wide, lds64 };
 struct GemmPlan {
   Gemm kernel;
@@ -549,7 +551,7 @@ GemmPlan pick_gemm(int M, int N, int K, int n_cu, size_t split_bytes, bool norm_
     if (k.k == Gemm::lds64 ? M <= 128
                            : (k.bm == 32 ? M > 32 : (k.bm == 64 ? M <= 32 || M > 128 : M <= 64)))
       continue;
-    if (k.k == Gemm::ring128x64 && M > 1024) continue;
+    if ((k.k == Gemm::ring128x64 || k.k == Gemm::ring128) && M > 1024) continue;
     const long t = (long)((M + k.bm - 1) / k.bm) * ((N + k.bn - 1) / k.bn);
     // with few rows the ring kernel of that tile is faster, but for an epilogue that the second
     // workgroup on the CU covers (output head of M = 256, N = 32000, K = 1024: 31.7 against 35.0 us)
@@ -570,7 +572,9 @@ GemmPlan pick_gemm(int M, int N, int K, int n_cu, size_t split_bytes, bool norm_
       float us = (float)rounds * ((float)(K / 64 / S) * step + k.tile_us +
                                   (k.k == Gemm::wide && S == 1 ? epi_us : 0.f));
       if (k.k == Gemm::lds64 && rounds > 1)  // two on a CU at a time
-        us = 2.f + (float)rounds * ((float)(K / 64) * (step - 0.07f) + 2.2f);
+        us = 2.f + (float)rounds * ((float)(K / 64) * (step - 0.07f) + 1.2f);
+      if (k.k == Gemm::lds128 && rounds == 1)  // short K: 5.2 .. 10.7 us at K = 128
+        us = std::max(us, (float)(K / 64) * 0.53f + 4.2f);
       if (S > 1) us += (float)S * M * N * (4.f / 4.2e6f) + (norm_follows ? 0.f : 3.4f);
       int tail = 1;
       const long left = t % n_cu;
