@@ -297,6 +297,11 @@ alr_status alr_set_rollout_graphs(alr_ctx* ctx, int32_t enable);
  *                invalid indices get ids -1, log-probs -inf, tail 0.
  *   logprobs_out DEVICE fp32 [n_anchor, block, vocab] or NULL (rows of -inf
  *                at invalid indices).  At least one label form must be given.
+ *                Without it the call may form its logits in products of other
+ *                shapes (all distinct positions at once), whose fp32 sums add in
+ *                another order: unlike in alr_rollout_topk, labels then agree
+ *                with those of a call that returns log-probs, and with slot 0 of
+ *                a rollout, up to rounding, and ids may swap at near ties.
  *   corpus_logp_out DEVICE fp32 [n_anchor, block]: log p_T(x_{a+s+1} |
  *                x_{<=a+s}); nan when a+s+1 is past the end or holds a given
  *                input row (alr_prefill's embeds) instead of a token.

@@ -3,7 +3,7 @@
 // bf16 path: MFMA with fp32 accumulation.  Large GEMMs use 256x256 tiles with a
 // hand-scheduled K loop (gemm_wide.hpp), products of few rows
 // gemm_bf16_ring_kernel, and what lies between the LDS-staged gemm_bf16_kernel at
-// 128x128.
+// 128x128 or 64x128 (its other tiles serve the debug entry point alone).
 // fp32 path: FMA, 64x64x16 tiles, or 8x64 ones with K shared by a workgroup's
 // waves where there are few.  Both hand the epilogue *pairs* of outputs:
 // the value at column c and the one at column c+32, where c lies in the low
