@@ -70,23 +70,25 @@ def site_work(site: str, w, anchor_seq=None, anchor_pos=None) -> dict:
     raise KeyError(site)
 
 
-# rocprofv3 counter summaries: launch site -> (summary file, kernel sources it was taken on)
+# rocprofv3 counter summaries: (workload, launch site) -> (summary file, kernel sources it was taken on)
 PROFILE_FILES = {
-    "prefill_gu": ("profiles/gemm_gate_up_prefill_llama8b_like.md",
-                   ("paper_2609_38795_amd/csrc/gemm_kernels.hpp",
-                    "paper_2609_38795_amd/csrc/device_common.hpp")),
+    ("llama8b_like", "prefill_gu"): (
+        "profiles/gemm_gate_up_prefill_llama8b_like.md",
+        ("paper_2609_38795_amd/csrc/gemm_wide.hpp",
+         "paper_2609_38795_amd/csrc/gemm_kernels.hpp",
+         "paper_2609_38795_amd/csrc/device_common.hpp")),
 }
 
 
-def measured_traffic(site: str):
-    """HBM bytes per launch from the committed counter summary, or None when the kernel
-    source has changed since the counters were taken (or none were taken)."""
+def measured_traffic(workload: str, site: str):
+    """HBM bytes per launch from the committed counter summary, or None when none was taken
+    of this workload's launches or the kernel source has changed since."""
     import hashlib
     import re
 
-    if site not in PROFILE_FILES:
+    if (workload, site) not in PROFILE_FILES:
         return None
-    path, srcs = PROFILE_FILES[site]
+    path, srcs = PROFILE_FILES[workload, site]
     try:
         text = open(os.path.join(ROOT, path)).read()
         h = hashlib.sha256()
@@ -272,7 +274,7 @@ def main():
         peak = PEAK_HBM_GBS
     roofline = {"bound": work["bound"], "achieved": round(achieved, 2), "peak": peak,
                 "unit": work["unit"], "frac": round(achieved / peak, 4),
-                "traffic": measured_traffic(args.site),
+                "traffic": measured_traffic(w.name, args.site),
                 "kernel": args.site, "avg_launch_ms": round(avg_s * 1e3, 4),
                 "launches_timed": site_n}
 
