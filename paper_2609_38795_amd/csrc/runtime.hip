@@ -501,7 +501,10 @@ bool launch_splitk_resid_norm(alr_ctx* ctx, int S, int M, int N, const EpiResid&
 // 4.0 + 3.1 sliced; M = 256 11.5 whole, 6.4 + 3.7 sliced).  The constants are fits to
 // products that store plain fp32 rows, M = 7 .. 8192, N = 64 .. 37888, K = 64 .. 18944
 // (weights rotated through more than the last-level cache).  The epilogues of the model are
-// in them for the 256x256 kernel alone (epi_us); with theirs the 128x128 LDS-staged
+// in them for the 256x256 kernel (epi_us) and, in part, for a round of 128x128 LDS-staged tiles
+// up to K = 512, as 64x128 ones lose less by theirs, two on a CU (prefills of 4 layers, d_model
+// 256, 2830 rows 321 -> 305 us, 3668 rows 326 -> 311; 61 others with d_model 128 to 1024, 1924 to
+// 16128 rows: 0.99 to 1.04 times as fast).  With longer K the 128x128 LDS-staged
 // tiles take longer than estimated (rollout O of 1024 x 4096 x 4096 50 us for 39, down of
 // 8192 x 1024 x 2816 68 for 56, O of 8192 x 1024 x 1024 32 for 23).  A step of the 256x256
 // kernel takes longer the more CUs run it, as the clock falls: 1.03 us on half of them,
@@ -574,7 +577,7 @@ GemmPlan pick_gemm(int M, int N, int K, int n_cu, size_t split_bytes, bool norm_
       if (k.k == Gemm::lds64 && rounds > 1)  // two on a CU at a time
         us = 2.f + (float)rounds * ((float)(K / 64) * (step - 0.07f) + 1.2f);
       if (k.k == Gemm::lds128 && rounds == 1)  // short K: 5.2 .. 10.7 us at K = 128
-        us = std::max(us, (float)(K / 64) * 0.53f + 4.2f);
+        us = std::max(us, (float)(K / 64) * 0.53f + 4.2f) + (K <= 512 ? 0.2f * epi_us : 0.f);
       if (S > 1) us += (float)S * M * N * (4.f / 4.2e6f) + (norm_follows ? 0.f : 3.4f);
       int tail = 1;
       const long left = t % n_cu;

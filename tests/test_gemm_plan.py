@@ -49,6 +49,15 @@ def test_where_64x128_tiles_are_taken():
     assert plan(300, W.get("llama8b_like").shape, "prefill_o") == RING128X64
 
 
+@pytest.mark.parametrize("d_model,rows,kernel", [
+    (256, 2830, LDS64), (512, 3072, LDS64),  # a round of 138 and 216 tiles of 128x128 would do
+    (576, 3072, LDS128)])
+def test_short_k_with_an_epilogue_takes_64x128_tiles(d_model, rows, kernel):
+    s = dataclasses.replace(W.get("small_bf16").shape, d_model=d_model, n_heads=4, n_kv_heads=4,
+                            head_dim=96 if d_model > 256 else 64)
+    assert _plan(s, "prefill_qkv", rows, anchors=1) == (kernel, 1, 1)
+
+
 def test_plan_errors():
     s = W.get("small_bf16").shape
     for bad in (dict(site="prefill_attn"), dict(rows=0), dict(cols=32), dict(n_cu=0)):
