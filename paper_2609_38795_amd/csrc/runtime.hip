@@ -574,6 +574,13 @@ GemmPlan pick_gemm(int M, int N, int K, int n_cu, size_t split_bytes, bool norm_
       }
       float us = (float)rounds * ((float)(K / 64 / S) * step + k.tile_us +
                                   (k.k == Gemm::wide && S == 1 ? epi_us : 0.f));
+      // short K: in the model 64x128 LDS-staged tiles gain what the fits to single products leave
+      // out (4 layers: 288 rows, K = 512 233 -> 226 us, 1000 rows, K = 256 208 -> 201), but not
+      // with a smaller A (400 rows, K = 256 164 -> 166) nor in steps of 32 (518 rows, K = 320
+      // 166 -> 169)
+      if (k.k == Gemm::ring128x64 && M > FEW_ROWS && K <= 640 && K % 128 == 0 &&
+          (long)M * K >= 1 << 17)
+        us += 1.f;
       if (k.k == Gemm::lds64 && rounds > 1)  // two on a CU at a time
         us = 2.f + (float)rounds * ((float)(K / 64) * (step - 0.07f) + 1.2f);
       if (k.k == Gemm::lds128 && rounds == 1)  // short K: 5.2 .. 10.7 us at K = 128

@@ -58,6 +58,15 @@ def test_short_k_with_an_epilogue_takes_64x128_tiles(d_model, rows, kernel):
     assert _plan(s, "prefill_qkv", rows, anchors=1) == (kernel, 1, 1)
 
 
+@pytest.mark.parametrize("d_model,rows,kernel", [
+    (512, 256, RING128X64), (512, 257, LDS64), (640, 700, LDS64), (256, 511, RING128X64),
+    (256, 512, LDS64), (576, 300, RING128X64)])
+def test_short_k_of_some_hundred_rows(d_model, rows, kernel):
+    """Gate/up of 512 columns: 64x128 tiles from 128 K elements of A on, where K is whole 128s."""
+    s = dataclasses.replace(W.get("small_bf16").shape, d_model=d_model, d_ffn=256)
+    assert _plan(s, "prefill_gu", rows, anchors=1) == (kernel, 1, 1)
+
+
 def test_plan_errors():
     s = W.get("small_bf16").shape
     for bad in (dict(site="prefill_attn"), dict(rows=0), dict(cols=32), dict(n_cu=0)):
